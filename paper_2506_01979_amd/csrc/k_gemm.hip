@@ -22,56 +22,57 @@ int device_cus() {
   return cus;
 }
 
-// Token-tile counts and tiles per pass with a kernel (token tiles rounded
-// up; padded rows read as zero).  A kernel for 5 token tiles (65 .. 80
-// rows) took the 13B step at 65 rows and prefix 8192 from 9.36 to 9.24 ms
-// against padding to 6.
-constexpr int kTTs[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
+// Tiles per pass with a k_gemm kernel.
 constexpr int kNTs[] = {1, 2, 3, 4, 6, 8};
 
 }  // namespace
 
-// Token tiles past which the projections take k_gemm_wide (from 5 token
-// tiles, 13B at 65 rows: QKV 35 -> 46 us, down 37 -> 41, gate/up 61 -> 61).
-constexpr int kWideFrom = 8;
+// Token tiles past which every projection takes k_gemm_wide (its comment has
+// both sides measured: at 5 tiles it is ahead on all of them, at 3 behind).
+constexpr int kWideFrom = 4;
+
+// Wide plan: the fewest token blocks of at most kWideTtCap tiles; the tile
+// groups fill the compute units; a group's tiles go in as few passes over K
+// as the accumulators allow.  The residual projections also split K over the
+// S <= kMaxSplit workgroups that make the bytes a workgroup moves, passes
+// (tiles + token tiles) / S, least (fewer slices on ties; 13B down at 129
+// rows: S = 4 35 us, S = 2 48).
+static GemmPlan plan_wide(int epi, int tiles, int ks, int tt_all, int cus) {
+  GemmPlan p{};
+  p.wide = 1;
+  p.tblocks = (tt_all + kWideTtCap - 1) / kWideTtCap;
+  p.tt = (tt_all + p.tblocks - 1) / p.tblocks;
+  const int cap = kWidePairs / p.tt < kWideNtCap ? kWidePairs / p.tt : kWideNtCap;
+  const int most = epi == EPI_RESID ? kMaxSplit : 1;
+  long long best = 0;
+  for (int S = 1; S <= most && (S == 1 || S * 4 <= ks); ++S) {
+    int groups = cus / (p.tblocks * S);
+    if (groups < 1) groups = 1;
+    if (groups > tiles) groups = tiles;
+    const int per_wg = (tiles + groups - 1) / groups;
+    const int passes = (per_wg + cap - 1) / cap;
+    int nt = (per_wg + passes - 1) / passes;
+    if (nt < 2) nt = 2;
+    const long long cost = 12LL * passes * (nt + p.tt) / S;  // 12: whole for every S
+    if (S == 1 || cost < best) {
+      best = cost;
+      p.nt = nt;
+      p.split = S;
+      p.groups = groups;
+    }
+  }
+  p.grid = p.tblocks * p.split * p.groups;
+  return p;
+}
 
 GemmPlan plan_gemm(int epi, int tiles, int ks, int n_tok) {
   GemmPlan p{};
   const int nc = ks / 8;
   const int tt_all = (n_tok + 15) / 16;
-  // Wide trees: k_gemm_wide (a wave owns a tile pair over one of KS parts
-  // of the workgroup's K range; the activation is staged once per 16 / KS
-  // tiles through LDS).  QKV and the residual projections, with the fewest
-  // tiles, take KS = 4; the residual projections also split K over up to
-  // kMaxSplit workgroups per tile group.  The LM head runs without its
-  // fused statistics (the separate pass reads the logits).  13B at 129
-  // rows: gate/up 120 -> 78 us, QKV 69 -> 61, down 61 -> 50 (KS = 2; KS = 4
-  // took the step from 13.20 to 13.11 ms), the LM head 138 + 5 -> 79 + 11
-  // with the statistics pass.
-  if (tt_all > kWideFrom &&
-      (epi == EPI_QKV || epi == EPI_SWIGLU || epi == EPI_RESID || epi == EPI_LOGITS)) {
-    const int KS = (epi == EPI_QKV || epi == EPI_RESID) ? 4 : 2;
-    p.wide = KS;
-    p.tt = tt_all <= 9 ? 9 : tt_all <= 12 ? 12 : 16;
-    p.nt = 2;
-    p.groups = (tiles + 16 / KS - 1) / (16 / KS);
-    int S = 1;
-    if (epi == EPI_RESID) {
-      S = device_cus() / p.groups;
-      if (S > kMaxSplit) S = kMaxSplit;
-      if (S * KS > ks) S = ks / KS;
-      if (S < 1) S = 1;
-    }
-    p.split = S;
-    p.grid = p.groups * S;
-    return p;
-  }
   const int cus = device_cus();
-  for (int v : kTTs)
-    if (v >= tt_all) {
-      p.tt = v;
-      break;
-    }
+  if (tt_all > kWideFrom) return plan_wide(epi, tiles, ks, tt_all, cus);
+  p.tt = tt_all;
+  p.tblocks = 1;
   // Projections that add into the residual stream have as many tiles as the
   // model is wide, about one per compute unit: they split K so that each
   // workgroup owns several tiles; the next RMSNorm sums the partial deltas.
@@ -83,7 +84,7 @@ GemmPlan plan_gemm(int epi, int tiles, int ks, int n_tok) {
   int groups = cus / S;
   if (groups > tiles) groups = tiles;
   const int per_wg = (tiles + groups - 1) / groups;
-  const int cap = gemm_nt_cap(p.tt);
+  const int cap = kGemmNtCap;
   const int passes = (per_wg + cap - 1) / cap;
   const int need = (per_wg + passes - 1) / passes;
   for (int v : kNTs)
@@ -100,7 +101,7 @@ GemmPlan plan_gemm(int epi, int tiles, int ks, int n_tok) {
 bool resid_norm_fusable(int tiles, int ks, int n_tok, int *groups) {
   const GemmPlan p = plan_gemm(EPI_RESID_NORM, tiles, ks, n_tok);
   if (groups) *groups = p.groups;
-  return n_tok <= kNormFuseRows && p.groups <= kSsGroups &&
+  return n_tok <= kNormFuseRows && !p.wide && p.groups <= kSsGroups &&
          (tiles + p.groups - 1) / p.groups <= p.nt && p.nt * p.tt <= kRedPairs;
 }
 
@@ -121,6 +122,7 @@ hipError_t launch_gemm(int epi, const GemmArgs &a, int tiles, int *split, hipStr
   b.tiles = tiles;
   b.split = p.split;
   b.groups = p.groups;
+  b.tblocks = p.tblocks;
   if (split) *split = p.split;
   switch (epi) {
     case EPI_QKV: return launch_gemm_qkv(b, p, s);

@@ -1,7 +1,7 @@
 // Skinny matrix-core GEMM kernel with fused epilogues (gfx950), included
 // by one translation unit per epilogue kind.
 //
-// The verify forward multiplies n_rows (5..256) activation rows by every
+// The verify forward multiplies n_rows (1..256) activation rows by every
 // weight matrix once; the weights (13-140 GB) dominate the bytes, so the
 // GEMM streams each weight tile from HBM exactly once with 16-byte loads in
 // the operand order of v_mfma_f32_16x16x32_bf16 (the layout sb_pack_weight
@@ -562,225 +562,236 @@ __global__ __launch_bounds__(kGemmThreads, 1) void k_gemm(GemmArgs a) {
 }
 
 
-// Wide GEMM (trees of more than 8 token tiles).
+// Wide GEMM (trees of more than 4 token tiles): the chunk-major scheme with 4
+// waves of 512 registers each instead of 8 of 256.
 //
-// A wave owns two 16-row weight tiles (a tile pair) over one of KS parts of
-// the workgroup's K range; the 8 / KS pairs of a workgroup (16 / KS tiles)
-// share the activation, staged through LDS one chunk at a time: chunk c
-// holds k-step c of every K part for all TT token tiles (KS TT fragments of
-// 1 KB; the waves load them into registers L chunks ahead, with the
-// weights, and write each chunk to one of two LDS buffers when it is due).
-// Each fragment read from LDS feeds both tiles of the pair, each weight
-// fragment all TT token tiles.  At the end the KS partial sums of each tile
-// meet in LDS and the owner wave of the tile runs the epilogue.  Split-K
-// launches (the residual projections, whose tile groups are too few to fill
-// the chip) also give each of `split` workgroups per tile group a
-// contiguous K range; the unit order is K-range-major, so each XCD caches
-// one range of the activation.  (Staging by direct-to-LDS loads into
-// separate LDS arrays, one per ring buffer, ran the step equally fast; into
-// one array the compiler waits for every load in flight before each LDS
-// read, since it cannot tell the buffers apart.)
-template <int TT, int KS>
-struct WideCfg {
-  static constexpr int PAIRS = kGemmWaves / KS;                     // tile pairs per workgroup
-  static constexpr int FRAG = KS * TT;                              // fragments per chunk
-  static constexpr int FPW = (FRAG + kGemmWaves - 1) / kGemmWaves;  // per wave, at most
-  static constexpr int FULL = FRAG % kGemmWaves == 0 ? kGemmWaves : FRAG % kGemmWaves;
-  static constexpr int L = FRAG <= 18 ? 6 : FRAG <= 36 ? 4 : 2;     // chunks in flight
-  static constexpr int LDS = 2 * FRAG > kGemmWaves * TT ? 2 * FRAG : kGemmWaves * TT;  // KB
-  static_assert(L % 2 == 0, "the unrolled chunk steps cover both LDS buffers");
-  static_assert((L - 1) * (FPW + 2) <= 63, "the loads in flight fit the wait counter");
-  static_assert(LDS <= 160, "the chunk buffers and the reduction fit LDS");
+// Past 4 token tiles the activation, not the weights, is most of what a
+// workgroup reads: a workgroup of m weight rows and t token rows moves
+// (m + t) 2 K bytes through its compute unit's L1, whose path sustains about
+// 50 GB/s of the mixed HBM / L2 stream here (80 GB/s from L2 alone), and that
+// sets the time (13B gate/up at 129 rows: 283 MB of weights, 48 us at the
+// rate of a long read; all loads from L1, 21 us of products).  m + t is
+// least for one pass over K with the largest m t a workgroup can accumulate.
+// Four waves, one per SIMD, hold 256 accumulator registers each (NT TT <= 64
+// tile pairs) beside a ring of R steps of loads; the K-split over the waves
+// means every byte is loaded once per workgroup, straight into registers,
+// with no LDS and no barrier in the main loop.  More than 9 token tiles are
+// cut into two token blocks, in workgroups next to each other on one XCD
+// (they share the weights through its L2).  Measured against the form that
+// staged the activation through LDS for 8 waves (13B, 129 rows / 7B, 256
+// rows): QKV 63 -> 43 / 90 -> 38 us, gate/up 81 -> 68 / 91 -> 70, down 49 ->
+// 35 / 57 -> 36, O 25 -> 18 / 30 -> 19; at 65 rows against k_gemm: gate/up 62 -> 48, down 39 ->
+// 27, QKV 36 -> 32, LM head 79 -> 56.  At 33 rows k_gemm's deeper ring and 8
+// waves win (QKV 27 against 28, O 11 against 13), so this form starts at 5
+// token tiles.  The activation through a ring in LDS (direct-to-LDS loads,
+// 1.5 to 2 times the bytes in flight) measured level with it.
+constexpr int kWideThreads = 256;
+constexpr int kWideWaves = kWideThreads / 64;
+constexpr int kWideRedPairs = 40;  // accumulators per LDS reduction round (160 KB)
+constexpr int kPastEnd = 0x40000000;  // a scalar offset past the end of any operand of a pass
+
+// Ring depth: as many steps as about 200 registers hold, at most 6; two for
+// the 9 x 7 form, which spills with three (13B gate/up at 129 rows: 58 us with
+// 2, 80 with 3; the 8 x 8 form does not: 7B LM head at 256 rows, 2 slots 118
+// us, 3 slots 94).
+template <int TT, int NT>
+struct WideRing {
+  static constexpr int r = 212 / (4 * (NT + TT));
+  static constexpr int R = TT == 9 && NT == 7 ? 2 : r > 6 ? 6 : r;
+  static_assert(R >= 2, "a step in flight beside the one multiplied");
+  static_assert(NT * TT <= kWidePairs, "the accumulators fit 256 registers");
 };
 
-template <int EPI, int TT, int KS>
-__global__ __launch_bounds__(kGemmThreads, 1) void k_gemm_wide(GemmArgs a) {
-  using C = WideCfg<TT, KS>;
-  constexpr int L = C::L, FPW = C::FPW;
-  constexpr int NW = 2;  // weight loads per wave per chunk (one per tile)
-  __shared__ __attribute__((aligned(16))) char abuf[C::LDS * 1024];
+// SHARED: another workgroup reads the same weights (token blocks); else they
+// are read once and marked non-temporal.
+template <int EPI, int TT, int NT, bool SHARED>
+__global__ __launch_bounds__(kWideThreads, 1) void k_gemm_wide(GemmArgs a) {
+  __shared__ f32x4 red[kWideWaves][kWideRedPairs][64];
+  constexpr int R = WideRing<TT, NT>::R;
+  constexpr int TPR = kWideRedPairs / TT;  // tiles per reduction round
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int ks = a.ks;
-  const int nb = gridDim.x;
-  const int u = (nb & 7) == 0 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
-  const int split = u / a.groups, grp = u - split * a.groups;
-  const int pw = w % C::PAIRS, kp = w / C::PAIRS;  // tile pair, K part
-  const int tile0 = (grp * C::PAIRS + pw) * 2;
-  const bool has = tile0 < a.tiles;  // wave-uniform
-  // K part q of the Q = split KS parts of the launch: k-steps [kb(q), kb(q+1))
-  const int Q = a.split * KS;
-  auto kb = [&](int q) { return ks * q / Q; };
-  const int nchunk = (ks + Q - 1) / Q;  // chunks: one k-step of every part
+  // work unit (K range, tile group, token block), XCD-major, the token block
+  // fastest and the K range slowest (an XCD reads few ranges of the activation)
+  const int xcd = blockIdx.x & 7, left = gridDim.x & 7;
+  const int u = xcd * (gridDim.x >> 3) + (xcd < left ? xcd : left) + (blockIdx.x >> 3);
+  const int tb = SHARED ? u % a.tblocks : 0, sg = SHARED ? u / a.tblocks : u;
+  const int split = sg / a.groups, grp = sg - split * a.groups;
+  const int t_lo = (int)(((long long)a.tiles * grp) / a.groups);
+  const int t_hi = (int)(((long long)a.tiles * (grp + 1)) / a.groups);
+  const int nc = ks / kWideWaves;  // chunks: one k-step per wave
+  const int c_begin = (nc * split) / a.split;
+  const int n_ch = (nc * (split + 1)) / a.split - c_begin;
+  const int tok0 = tb * TT * 16;
   const int xbytes = ((a.n_tok + 15) >> 4) * ks * 1024;
   const __amdgpu_buffer_rsrc_t xrs =
       __builtin_amdgcn_make_buffer_rsrc((void *)a.X, 0, xbytes, kBufferDword3);
-  const int wbytes = a.tiles * ks * 1024;
-  const __amdgpu_buffer_rsrc_t wrs =
-      __builtin_amdgcn_make_buffer_rsrc((void *)a.W, 0, wbytes, kBufferDword3);
-  const int qw = split * KS + kp;  // this wave's K part
-  const int kw0 = kb(qw), kwn = kb(qw + 1) - kw0;
-  int wvo[NW];
-#pragma unroll
-  for (int j = 0; j < NW; ++j)
-    wvo[j] = tile0 + j < a.tiles ? (tile0 + j) * ks * 1024 + lane * 16 : wbytes;
-  // waves w < FULL move FPW fragments per chunk, the others FPW - 1
-  const bool full = w < C::FULL;
-
-  // Chunk c's fragment f = p TT + tt (K part p, token tile tt) sits at KB f
-  // of its buffer; wave w moves fragments w + 8 j.  Lane l loads bytes
-  // 16 l .. of a fragment (token row r = l / 4, k 8 (l % 4) ..) and stores
-  // them at 16-byte slot 4 r + ((l % 4) ^ x(r)), x(r) = (r / 2 ^ r / 8) % 4:
-  // the 8 (16) lanes that a 128-bit LDS access serves per clock then cover
-  // all 32 (64) banks, for the writes and for the operand reads.
-  auto xsw = [](int r) { return ((r >> 1) ^ (r >> 3)) & 3; };
-  const int wsw = ((lane >> 2) * 4 + ((lane & 3) ^ xsw(lane >> 2))) * 16;
-  const int rsw = ((lane & 15) * 4 + ((lane >> 4) ^ xsw(lane & 15))) * 16;
-  // per fragment of this wave: its lane offset at k-step 0 of its K part
-  // and the part's length (the loop below only adds the chunk)
-  int xoff[FPW], xlen[FPW];
-#pragma unroll
-  for (int j = 0; j < FPW; ++j) {
-    const int f = w + kGemmWaves * j;
-    const int p = f / TT, tt = f - p * TT;
-    const int q = split * KS + p;
-    const int k0 = kb(q);
-    xoff[j] = (tt * ks + k0) * 1024 + lane * 16;
-    xlen[j] = kb(q + 1) - k0;
-  }
-  i32x4 xr[L][FPW], wr[L][NW];
-  auto issue = [&](int c, int slot) {
-#pragma unroll
-    for (int j = 0; j < FPW; ++j)
-      if (j < FPW - 1 || full)
-        xr[slot][j] = __builtin_amdgcn_raw_buffer_load_b128(
-            xrs, c < xlen[j] ? xoff[j] + c * 1024 : xbytes, 0, 0);
-    const bool in = c < kwn;
-#pragma unroll
-    for (int j = 0; j < NW; ++j)
-      wr[slot][j] = __builtin_amdgcn_raw_buffer_load_b128(wrs, in ? wvo[j] : wbytes,
-                                                          (kw0 + (in ? c : 0)) * 1024, kNonTemporal);
+  // Lane offset within a fragment; the fragment and k-step come as the scalar
+  // offset.  Token tiles past the activation read past its end (zero).  The
+  // block's last tile has an offset of its own: its rows >= n_tok read zero
+  // too instead of moving bytes.
+  const int xlane = (lane & 15) * 64 + (lane >> 4) * 16;
+  const int xlast = tok0 + (TT - 1) * 16 + (lane & 15) < a.n_tok ? xlane : xbytes;
+  const int xtile = tb * TT * ks * 1024;
+  auto wdesc = [&](int gb) {
+    const int n = t_hi - gb < NT ? t_hi - gb : NT;
+    return __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)a.W + (size_t)gb * ks * 1024), 0,
+                                             n * ks * 1024, kBufferDword3);
   };
-  auto stage = [&](int slot, int buf) {
-#pragma unroll
-    for (int j = 0; j < FPW; ++j)
-      if (j < FPW - 1 || full)
-        *(i32x4 *)(abuf + (buf * C::FRAG + w + kGemmWaves * j) * 1024 + wsw) = xr[slot][j];
+  // Steps past the K range read past the end of both buffers (zero), so the
+  // loop runs whole rings without a remainder.
+  auto koff = [&](int c) { return c < n_ch ? ((c_begin + c) * kWideWaves + w) * 1024 : kPastEnd; };
+  i32x4 wr[R][NT], xr[R][TT];
+  auto load_x = [&](int r, int ko, int tt) {
+    xr[r][tt] = __builtin_amdgcn_raw_buffer_load_b128(xrs, tt == TT - 1 ? xlast : xlane,
+                                                      xtile + tt * ks * 1024 + ko, 0);
   };
-  f32x4 acc[NW][TT];
-#pragma unroll
-  for (int j = 0; j < NW; ++j)
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) acc[j][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto mac = [&](int buf, int slot) {
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-      // operand B: token row lane % 16, k 8 (lane / 16) .. of the fragment
-      const uint4 xv = *(const uint4 *)(abuf + (buf * C::FRAG + kp * TT + tt) * 1024 + rsw);
-#pragma unroll
-      for (int j = 0; j < NW; ++j)
-        acc[j][tt] = mfma16(__builtin_bit_cast(bf16x8, wr[slot][j]), as_bf16x8(xv), acc[j][tt]);
-    }
+  auto load_w = [&](const __amdgpu_buffer_rsrc_t &wrs, int r, int ko, int t) {
+    wr[r][t] = __builtin_amdgcn_raw_buffer_load_b128(wrs, lane * 16, t * ks * 1024 + ko,
+                                                     SHARED ? 0 : kNonTemporal);
   };
-  // One group of loads per chunk (its activation, then its weights), L
-  // groups ahead.  Step c writes chunk c + 1's activation to LDS while it
-  // multiplies chunk c, then one barrier: chunk c + 1 is visible for the
-  // next step and every wave is done with buffer c % 2, which the next step
-  // overwrites.  At step c the loads issued after chunk c + 1's group are
-  // L - 2 whole groups.
-  constexpr int AFTER_FULL = (L - 2) * (FPW + NW), AFTER_SHORT = (L - 2) * (FPW - 1 + NW);
-  auto wait_next = [&]() {
-    if (full)
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AFTER_FULL + FPW + NW) : "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AFTER_SHORT + FPW - 1 + NW) : "memory");
-  };
+  // the first R - 1 steps of a pass
+  auto fill = [&](const __amdgpu_buffer_rsrc_t &wrs) {
 #pragma unroll
-  for (int c = 0; c < L; ++c) issue(c, c);
-  wait_next();  // chunk 0
-  stage(0, 0);
-  lds_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  for (int c0 = 0; c0 < nchunk; c0 += L) {
+    for (int r = 0; r < R - 1; ++r) {
+      const int ko = koff(r);
 #pragma unroll
-    for (int i = 0; i < L; ++i) {
-      const int c = c0 + i;
-      if (c >= nchunk) break;  // uniform
-      if (full)
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AFTER_FULL) : "memory");
-      else
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AFTER_SHORT) : "memory");
-      stage((i + 1) % L, (i + 1) % 2);
-      if (has) mac(i % 2, i);
-      lds_barrier();
+      for (int tt = 0; tt < TT; ++tt) load_x(r, ko, tt);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) load_w(wrs, r, ko, t);
       __builtin_amdgcn_sched_barrier(0);
-      issue(c + L, i);
     }
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  // Reduction, one tile of the pairs per round: every wave leaves its
-  // partial sums of the pair's tile j in LDS; the wave of K part j adds the
-  // KS partials of its pair in part order and runs the epilogue.
-  f32x4(*red)[64] = (f32x4(*)[64])abuf;  // [wave][tt][lane]
+  };
+  if (t_lo < t_hi) fill(wdesc(t_lo));
+  for (int gb = t_lo; gb < t_hi; gb += NT) {
+    const int n_here = t_hi - gb < NT ? t_hi - gb : NT;
+    const __amdgpu_buffer_rsrc_t wrs = wdesc(gb);
+    f32x4 acc[NT][TT];
 #pragma unroll
-  for (int j = 0; j < NW; ++j) {
-    lds_barrier();
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) red[w * TT + tt][lane] = acc[j][tt];
-    lds_barrier();
-    const int tile = tile0 + j;
-    if (kp == j && tile < a.tiles) {
-#pragma unroll 1
-      for (int tt = 0; tt < TT; ++tt) {
-        f32x4 v = red[pw * TT + tt][lane];
+      for (int tt = 0; tt < TT; ++tt) acc[t][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // Step c: multiply slot r = c % R while refilling the slot of step c - 1
+    // with step c + R - 1, the loads spread between the products.
+    for (int c = 0; c < n_ch; c += R) {
 #pragma unroll
-        for (int p = 1; p < KS; ++p) v += red[(p * C::PAIRS + pw) * TT + tt][lane];
-        // lane l holds rows 4 (l / 16) .. + 3 of the tile for token row
-        // l % 16; lanes l < 32 take rows p0 = 4 (l / 16) .. + 3 and
-        // p0 + 8 .. + 3 (from lane l + 32)
-        f32x4 v2;
+      for (int r = 0; r < R; ++r) {
+        const int rn = (r + R - 1) % R;
+        const int ko = koff(c + r + R - 1);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v2[i] = __shfl_down(v[i], 32, 64);
-        const int tok = tt * 16 + (lane & 15);
-        if (lane < 32 && tok < a.n_tok) {
-          if ((EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LOGITS) && a.rs_in) {
-            const float r = a.rs_in[tok];
-            v *= r;
-            v2 *= r;
+        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+          for (int l = (NT + TT) * t / NT; l < (NT + TT) * (t + 1) / NT; ++l) {
+            if (l < TT)
+              load_x(rn, ko, l);
+            else
+              load_w(wrs, rn, ko, l - TT);
           }
-          epilogue4<EPI>(a, a.rope, split, tile, 4 * (lane >> 4), tok, v, v2);
+#pragma unroll
+          for (int tt = 0; tt < TT; ++tt)
+            acc[t][tt] = mfma16(__builtin_bit_cast(bf16x8, wr[r][t]),
+                                __builtin_bit_cast(bf16x8, xr[r][tt]), acc[t][tt]);
+          __builtin_amdgcn_sched_barrier(0);
         }
+      }
+    }
+    // the next pass's first loads run under this pass's reduction
+    if (gb + NT < t_hi) fill(wdesc(gb + NT));
+    // The 4 waves' partial sums, TPR tiles per LDS round, added in wave order;
+    // items as in k_gemm.
+#pragma unroll
+    for (int t0 = 0; t0 < NT; t0 += TPR) {
+      if (t0 < n_here) {
+#pragma unroll
+        for (int tl = 0; tl < TPR; ++tl)
+          if (t0 + tl < NT)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) red[w][tl * TT + tt][lane] = acc[t0 + tl][tt];
+        lds_barrier();
+        const int tiles_here = n_here - t0 < TPR ? n_here - t0 : TPR;
+        const int items = tiles_here * TT * 32;
+        for (int it = threadIdx.x; it < items; it += kWideThreads) {
+          const int tok16 = it & 15, g = (it >> 4) & 1, pr = it >> 5;
+          const int tl = pr / TT, tt = pr - tl * TT;
+          const int tok = tok0 + tt * 16 + tok16;
+          if (tok < a.n_tok) {
+            const int l1 = tok16 + 16 * g;
+            f32x4 v1 = red[0][pr][l1], v2 = red[0][pr][l1 + 32];
+#pragma unroll
+            for (int ww = 1; ww < kWideWaves; ++ww) {
+              v1 += red[ww][pr][l1];
+              v2 += red[ww][pr][l1 + 32];
+            }
+            if ((EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LOGITS) && a.rs_in) {
+              const float rs = a.rs_in[tok];
+              v1 *= rs;
+              v2 *= rs;
+            }
+            epilogue4<EPI>(a, a.rope, split, gb + t0 + tl, 4 * g, tok, v1, v2);
+          }
+        }
+        lds_barrier();
       }
     }
   }
 }
 
-template <int EPI, int TT, int KS>
-hipError_t launch_wide_tt(const GemmArgs &a, int grid, hipStream_t s) {
-  LaunchEvents &ev = g_launch_events;
-  if (!ev.taken) {
-    ev.taken = true;
-    hipExtLaunchKernelGGL((k_gemm_wide<EPI, TT, KS>), dim3(grid), dim3(kGemmThreads), 0, s,
-                          ev.start, ev.stop, 0, a);
+template <int EPI, int TT, int NT, bool SHARED>
+hipError_t launch_wide_nt(const GemmArgs &a, int grid, hipStream_t s) {
+  if constexpr (NT * TT > kWidePairs) {
+    return hipErrorInvalidValue;
   } else {
-    hipLaunchKernelGGL((k_gemm_wide<EPI, TT, KS>), dim3(grid), dim3(kGemmThreads), 0, s, a);
+    LaunchEvents &ev = g_launch_events;
+    if (!ev.taken) {
+      ev.taken = true;
+      hipExtLaunchKernelGGL((k_gemm_wide<EPI, TT, NT, SHARED>), dim3(grid), dim3(kWideThreads), 0, s,
+                            ev.start, ev.stop, 0, a);
+    } else {
+      hipLaunchKernelGGL((k_gemm_wide<EPI, TT, NT, SHARED>), dim3(grid), dim3(kWideThreads), 0, s, a);
+    }
+    return hipGetLastError();
   }
-  return hipGetLastError();
 }
 
-template <int EPI, int KS>
-hipError_t launch_wide_ks(const GemmArgs &a, int tt, int grid, hipStream_t s) {
-  switch (tt) {
-    case 9: return launch_wide_tt<EPI, 9, KS>(a, grid, s);
-    case 12: return launch_wide_tt<EPI, 12, KS>(a, grid, s);
-    case 16: return launch_wide_tt<EPI, 16, KS>(a, grid, s);
+template <int EPI, int TT, bool SHARED>
+hipError_t launch_wide_tt(const GemmArgs &a, int nt, int grid, hipStream_t s) {
+  switch (nt) {
+    case 2: return launch_wide_nt<EPI, TT, 2, SHARED>(a, grid, s);
+    case 3: return launch_wide_nt<EPI, TT, 3, SHARED>(a, grid, s);
+    case 4: return launch_wide_nt<EPI, TT, 4, SHARED>(a, grid, s);
+    case 5: return launch_wide_nt<EPI, TT, 5, SHARED>(a, grid, s);
+    case 6: return launch_wide_nt<EPI, TT, 6, SHARED>(a, grid, s);
+    case 7: return launch_wide_nt<EPI, TT, 7, SHARED>(a, grid, s);
+    case 8: return launch_wide_nt<EPI, TT, 8, SHARED>(a, grid, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <int EPI>
+hipError_t launch_wide(const GemmArgs &a, const GemmPlan &p, hipStream_t s) {
+  if (p.tblocks == 1) {
+    switch (p.tt) {
+      case 5: return launch_wide_tt<EPI, 5, false>(a, p.nt, p.grid, s);
+      case 6: return launch_wide_tt<EPI, 6, false>(a, p.nt, p.grid, s);
+      case 7: return launch_wide_tt<EPI, 7, false>(a, p.nt, p.grid, s);
+      case 8: return launch_wide_tt<EPI, 8, false>(a, p.nt, p.grid, s);
+      case 9: return launch_wide_tt<EPI, 9, false>(a, p.nt, p.grid, s);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  switch (p.tt) {
+    case 5: return launch_wide_tt<EPI, 5, true>(a, p.nt, p.grid, s);
+    case 6: return launch_wide_tt<EPI, 6, true>(a, p.nt, p.grid, s);
+    case 7: return launch_wide_tt<EPI, 7, true>(a, p.nt, p.grid, s);
+    case 8: return launch_wide_tt<EPI, 8, true>(a, p.nt, p.grid, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <int EPI, int TT, int NT>
 hipError_t launch_tt_nt(const GemmArgs &a, int grid, hipStream_t s) {
-  if constexpr (NT > gemm_nt_cap(TT)) {
+  if constexpr (NT > kGemmNtCap) {
     return hipErrorInvalidValue;
   } else {
     LaunchEvents &ev = g_launch_events;
@@ -812,11 +823,8 @@ hipError_t launch_tt(const GemmArgs &a, int nt, int grid, hipStream_t s) {
 // tiles and tiles per pass).
 template <int EPI>
 hipError_t launch_epi(const GemmArgs &b, const GemmPlan &p, hipStream_t s) {
-  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_RESID || EPI == EPI_LOGITS) {
-    if (p.wide == 2) return launch_wide_ks<EPI, 2>(b, p.tt, p.grid, s);
-  }
-  if constexpr (EPI == EPI_QKV || EPI == EPI_RESID) {
-    if (p.wide == 4) return launch_wide_ks<EPI, 4>(b, p.tt, p.grid, s);
+  if constexpr (EPI != EPI_RESID_NORM) {
+    if (p.wide) return launch_wide<EPI>(b, p, s);
   }
   if (p.wide) return hipErrorInvalidValue;
   switch (p.tt) {
@@ -824,11 +832,6 @@ hipError_t launch_epi(const GemmArgs &b, const GemmPlan &p, hipStream_t s) {
     case 2: return launch_tt<EPI, 2>(b, p.nt, p.grid, s);
     case 3: return launch_tt<EPI, 3>(b, p.nt, p.grid, s);
     case 4: return launch_tt<EPI, 4>(b, p.nt, p.grid, s);
-    case 5: return launch_tt<EPI, 5>(b, p.nt, p.grid, s);
-    case 6: return launch_tt<EPI, 6>(b, p.nt, p.grid, s);
-    case 8: return launch_tt<EPI, 8>(b, p.nt, p.grid, s);
-    case 12: return launch_tt<EPI, 12>(b, p.nt, p.grid, s);
-    case 16: return launch_tt<EPI, 16>(b, p.nt, p.grid, s);
     default: return hipErrorInvalidValue;
   }
 }

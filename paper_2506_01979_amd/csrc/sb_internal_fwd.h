@@ -95,6 +95,7 @@ struct GemmArgs {
   int out_rows;        // RESID: hidden; LOGITS: vocab
   int epi;             // EPI_*
   int split, groups;   // K ranges, tile groups (grid = split * groups)
+  int tblocks;         // k_gemm_wide: token blocks (grid = tblocks * split * groups)
   float *h;            // RESID output: projection delta slices, fp32 [split][n_tok][out_rows]
   float *logits;       // LOGITS output
   uint16_t *act;       // SWIGLU output (packed, act_ks k-steps)
@@ -134,7 +135,7 @@ struct GemmArgs {
 // launch (its largest group count).
 constexpr int kSsGroups = 256;
 // Largest token count of a RESID_NORM launch and its consumer.
-constexpr int kNormFuseRows = 128;
+constexpr int kNormFuseRows = 64;
 
 struct AttnArgs {
   const void *q;        // bf16 or f32 [rows][n_heads][d]
@@ -187,16 +188,19 @@ struct BranchArgs {
 hipError_t launch_branch(const BranchArgs &a, hipStream_t s);
 // Launch geometry of a GEMM: token tiles (rounded up to a kernel's), tiles per
 // pass, K split, tile groups and grid.
-// Largest tiles per pass of the GEMM kernel per token-tile count (its
-// register budget), and the (tile, token tile) accumulator pairs it reduces
-// per LDS round.
-constexpr int gemm_nt_cap(int tt) {
-  return tt <= 4 ? 8 : tt <= 6 ? 6 : tt <= 8 ? 4 : tt <= 12 ? 2 : 1;
-}
+// Largest tiles per pass of k_gemm (its register budget), and the (tile,
+// token tile) accumulator pairs it reduces per LDS round.
+constexpr int kGemmNtCap = 8;
 constexpr int kRedPairs = 16;
+// k_gemm_wide: most (tile, token tile) accumulator pairs and tiles of a pass,
+// most token tiles of a workgroup.
+constexpr int kWidePairs = 64;
+constexpr int kWideNtCap = 8;
+constexpr int kWideTtCap = 9;
 struct GemmPlan {
   int tt, nt, split, groups, grid;
-  int wide;  // k_gemm_wide with this many K parts per workgroup (0: k_gemm)
+  int wide;     // k_gemm_wide (0: k_gemm)
+  int tblocks;  // token blocks (k_gemm_wide)
 };
 GemmPlan plan_gemm(int epi, int tiles, int ks, int n_tok);
 // Launches of a planned GEMM, one per epilogue kind (k_gemm_*.hip).

@@ -183,6 +183,30 @@ def test_verify_forward_parity(api, sname, P, spec):
         assert np.array_equal(vp, np.asarray(Vp[:, :, :kv_len], np.float32))
 
 
+@pytest.mark.parametrize("sname,n", [("ragged_bf16", n) for n in (65, 80, 81, 97, 112, 128, 144, 145, 160, 177,
+                                                                  193, 209, 225, 241, 256)] +
+                         [("widevocab_bf16", n) for n in (65, 128, 144, 145, 209, 256)])
+def test_wide_gemm_token_tiles(api, sname, n):
+    """Every token-tile form of the wide GEMM (5 .. 9 tiles, and two blocks of
+    5 .. 8), at both edges of a tile, on ragged widths; and a vocabulary whose
+    LM head takes several passes per workgroup (33000 columns: 8 to 9 tiles a
+    group at one block, 16 to 17 at two)."""
+    shape = synth.SHAPES.get(sname) or synth.Shape(sname, 1, 256, 4, 2, 64, 520, 33000, "bf16")
+    say(f"wide GEMM {sname} n={n}")
+    parents = np.array([-1] + [(i - 1) // 3 for i in range(1, n)], np.int32)  # a bushy tree
+    toks = np.random.default_rng(n).integers(0, shape.vocab, n).astype(np.int32)
+    empty = np.zeros((shape.n_layers, shape.n_kv_heads, 0, shape.head_dim))
+    ref, kt, vt = decoder.tree_forward(shape, weights(shape), empty, empty, 0, toks, parents, "bf16")
+    st = []
+    m = model(api, shape)
+    got, k, v = gpu_forward(api, m, None, None, 0, toks, parents, stats_out=st)
+    assert row_relerr(got, ref) < tol(shape)
+    check_stats(st[0], got, 1.0)
+    kg, vg = m.read_kv(k, v, 0, n)
+    assert row_relerr(kg.reshape(-1, shape.head_dim), kt.reshape(-1, shape.head_dim)) < tol(shape) * 5
+    assert row_relerr(vg.reshape(-1, shape.head_dim), vt.reshape(-1, shape.head_dim)) < tol(shape) * 5
+
+
 @pytest.mark.parametrize("sname,kind,T", [
     ("small_bf16", "ties", 1.0), ("small_bf16", "ties", 0.0), ("ragged_bf16", "ties", 0.7),
     ("small_bf16", "nonfinite", 1.0), ("small_bf16", "nonfinite", 0.0),

@@ -239,6 +239,11 @@ sb_status forward_bf16(sb_model *m, const sb_kv_cache *kv, int kv_len, const int
   float *rs = (float *)(ws + L.rs);
 
   EmbedArgs ea = embed_args(m, tokens, h, n, kv_len, meta, rope);
+  ea.gain = m->layers[0].attn_norm;
+  ea.xa = xa;
+  ea.rs = rs;
+  ea.xa_ks = L.ks_h;
+  ea.eps = c.rms_eps;
   SB_TRY(launch_embed_meta(ea, tree, L.np, 1, s));
 
   const PackGeom gq = pack_geom(c, SB_W_QKV), go = pack_geom(c, SB_W_O),
@@ -291,9 +296,9 @@ sb_status forward_bf16(sb_model *m, const sb_kv_cache *kv, int kv_len, const int
     const sb_layer_weights &lw = m->layers[l];
     uint16_t *kc = (uint16_t *)kv->k + l * layer_kv;
     uint16_t *vc = (uint16_t *)kv->v + l * layer_kv;
-    SB_TIMED(SB_KC_NORM, launch_rmsnorm_pack(h, split ? delta : nullptr, split ? split : 1,
-                                             lw.attn_norm, H, L.ks_h, n, L.np, c.rms_eps, xa, rs,
-                                             s, tap_of(l - 1)));
+    if (l > 0)  // the embedding kernel applied the first layer's
+      SB_TIMED(SB_KC_NORM, launch_rmsnorm_pack(h, delta, split, lw.attn_norm, H, L.ks_h, n, L.np,
+                                               c.rms_eps, xa, rs, s, tap_of(l - 1)));
     ga.W = (const uint16_t *)lw.qkv;
     ga.X = xa;
     ga.ks = gq.ks;

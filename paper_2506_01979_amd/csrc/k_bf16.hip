@@ -9,6 +9,8 @@
 namespace sb {
 namespace {
 
+static_assert(SB_MAX_ROWS == 256, "k_embed_meta: one thread per row, four waves");
+
 // ---------------------------------------------------------------------------
 // packing
 // ---------------------------------------------------------------------------
@@ -91,18 +93,35 @@ __device__ __forceinline__ float load_embed<float>(const float *e, size_t i) {
   return e[i];
 }
 
+// One workgroup per row.  bf16 models also get the first layer's RMSNorm here
+// (a.gain set): the row is in registers anyway, so the norm costs no launch
+// of its own (68M draft, one row: 3 us of 87).  Ancestors by pointer doubling
+// over all rows at once, log2(n) rounds: following the parents one by one
+// took 32 us for a 256-row chain, this kernel now takes 6.
 template <typename ET>
-__global__ __launch_bounds__(256) void k_embed_meta(EmbedArgs a, TreeArg tree) {
+__global__ __launch_bounds__(SB_MAX_ROWS) void k_embed_meta(EmbedArgs a, TreeArg tree) {
   const int t = blockIdx.x;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  __shared__ int16_t s_jump[SB_MAX_ROWS];
+  __shared__ uint8_t s_on[SB_MAX_ROWS];  // row is on the path root..t
+  __shared__ int s_cnt[SB_MAX_ROWS / 64];
+  __shared__ float s_sq[SB_MAX_ROWS / 64];
+  // the tree: a kernel argument (a dynamically indexed read is a memory access)
+  int jump = (int)threadIdx.x < tree.n ? tree.parent[threadIdx.x] : -1;
+  s_jump[threadIdx.x] = (int16_t)jump;
+  s_on[threadIdx.x] = (int)threadIdx.x == t && t < tree.n;
   float *h = a.h + (size_t)t * a.hidden;
+  float sq = 0.0f;
+  constexpr int kMaxV = 8;
+  float4 lo[kMaxV], hi[kMaxV];
+  const bool vec = sizeof(ET) == 2 && (a.hidden & 7) == 0;
   if (t < a.n_tok) {
     int tok = a.tokens[t];
     tok = tok < 0 ? 0 : (tok >= a.vocab ? a.vocab - 1 : tok);  // ids are clamped
     const ET *e = (const ET *)a.embed + (size_t)tok * a.hidden;
-    if (sizeof(ET) == 2 && (a.hidden & 7) == 0) {
+    if (vec) {
       // bf16 rows: 8 elements per 16-byte load, every load of the row issued
       // before the first store (hidden <= 16384: at most 8 per thread)
-      constexpr int kMaxV = 8;
       uint4 v[kMaxV];
       const int nv = a.hidden >> 3;
 #pragma unroll
@@ -114,14 +133,15 @@ __global__ __launch_bounds__(256) void k_embed_meta(EmbedArgs a, TreeArg tree) {
       for (int j = 0; j < kMaxV; ++j) {
         const int i = threadIdx.x + j * 256;
         if (i < nv) {
-          const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-          float4 lo, hi;
-          lo.x = bf2f((uint16_t)(w[0] & 0xffff)); lo.y = bf2f((uint16_t)(w[0] >> 16));
-          lo.z = bf2f((uint16_t)(w[1] & 0xffff)); lo.w = bf2f((uint16_t)(w[1] >> 16));
-          hi.x = bf2f((uint16_t)(w[2] & 0xffff)); hi.y = bf2f((uint16_t)(w[2] >> 16));
-          hi.z = bf2f((uint16_t)(w[3] & 0xffff)); hi.w = bf2f((uint16_t)(w[3] >> 16));
-          ((float4 *)h)[2 * i] = lo;
-          ((float4 *)h)[2 * i + 1] = hi;
+          const uint32_t x[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+          lo[j].x = bf2f((uint16_t)(x[0] & 0xffff)); lo[j].y = bf2f((uint16_t)(x[0] >> 16));
+          lo[j].z = bf2f((uint16_t)(x[1] & 0xffff)); lo[j].w = bf2f((uint16_t)(x[1] >> 16));
+          hi[j].x = bf2f((uint16_t)(x[2] & 0xffff)); hi[j].y = bf2f((uint16_t)(x[2] >> 16));
+          hi[j].z = bf2f((uint16_t)(x[3] & 0xffff)); hi[j].w = bf2f((uint16_t)(x[3] >> 16));
+          ((float4 *)h)[2 * i] = lo[j];
+          ((float4 *)h)[2 * i + 1] = hi[j];
+          sq += (lo[j].x * lo[j].x + lo[j].y * lo[j].y) + (lo[j].z * lo[j].z + lo[j].w * lo[j].w) +
+                (hi[j].x * hi[j].x + hi[j].y * hi[j].y) + (hi[j].z * hi[j].z + hi[j].w * hi[j].w);
         }
       }
     } else {
@@ -130,39 +150,63 @@ __global__ __launch_bounds__(256) void k_embed_meta(EmbedArgs a, TreeArg tree) {
   } else {
     for (int k = threadIdx.x; k < a.hidden; k += blockDim.x) h[k] = 0.0f;
   }
-  // this row's depth, position and ancestor mask, then its RoPE angles.
-  // The tree (kernel arguments: a dynamically indexed read is a memory
-  // access) goes to LDS in one parallel copy before the parent chase.
-  __shared__ int s_pos;
-  __shared__ int16_t s_par[SB_MAX_ROWS];
-  for (int i = threadIdx.x; i < tree.n; i += blockDim.x) s_par[i] = tree.parent[i];
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int depth = 0;
-    if (t < tree.n) {
-      int j = t;
-      for (int guard = 0; guard < SB_MAX_ROWS && j >= 0; ++guard) {
-#pragma unroll
-        for (int w = 0; w < 8; ++w)
-          if (w == (j >> 5)) m[w] |= 1u << (j & 31);
-        j = s_par[j];
-        if (j >= 0) ++depth;
-      }
-    }
-    s_pos = a.kv_len + depth;
-    a.meta->pos[t] = a.kv_len + depth;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) a.meta->anc[t][w] = m[w];
+  // round r: every row on the path marks its 2^r-th ancestor, then all jumps
+  // double.  A mark seen within its own round only adds true ancestors.
+  for (int step = 1; step < tree.n; step <<= 1) {
+    const int next = jump >= 0 ? s_jump[jump] : -1;
+    if (jump >= 0 && s_on[threadIdx.x]) s_on[jump] = 1;
+    __syncthreads();
+    jump = next;
+    s_jump[threadIdx.x] = (int16_t)next;
+    __syncthreads();
+  }
+  const unsigned long long on = __ballot(s_on[threadIdx.x] != 0);
+  if (lane < 2) a.meta->anc[t][2 * w + lane] = (uint32_t)(on >> (32 * lane));
+  if (lane == 0) s_cnt[w] = __popcll(on);
+  if (sizeof(ET) == 2 && a.gain) {
+    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+    if (lane == 0) s_sq[w] = sq;
   }
   __syncthreads();
+  const int rows = (s_cnt[0] + s_cnt[1]) + (s_cnt[2] + s_cnt[3]);
+  const int pos = a.kv_len + (rows > 0 ? rows - 1 : 0);
+  if (threadIdx.x == 0) a.meta->pos[t] = pos;
   if (a.rope && t < a.n_tok) {
     const int half = a.head_dim / 2;
     for (int j = threadIdx.x; j < half; j += blockDim.x) {
-      const double ang = (double)s_pos * a.theta[j];
+      const double ang = (double)pos * a.theta[j];
       double sn, cs;
       sincos(ang, &sn, &cs);
       a.rope[t * half + j] = make_float2((float)cs, (float)sn);
+    }
+  }
+  // the first layer's norm in factored form, as k_rmsnorm_pack writes it
+  if (sizeof(ET) == 2 && a.gain) {
+    const int gbytes = a.hidden * 4;
+    const __amdgpu_buffer_rsrc_t grs =
+        __builtin_amdgcn_make_buffer_rsrc((void *)a.gain, 0, gbytes, kBufferDword3);
+    f32x4 gv[kMaxV][2];
+#pragma unroll
+    for (int j = 0; j < kMaxV; ++j)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
+        gv[j][hh] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  grs, (threadIdx.x + j * 256) * 32 + hh * 16, 0, 0));
+    const float mean = ((s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3])) / (float)a.hidden;
+    if (threadIdx.x == 0) a.rs[t] = t < a.n_tok ? 1.0f / sqrtf(mean + a.eps) : 0.0f;
+#pragma unroll
+    for (int j = 0; j < kMaxV; ++j) {
+      const int i = threadIdx.x + j * 256;
+      if (i >= a.xa_ks * 4) break;
+      uint4 o = make_uint4(0, 0, 0, 0);  // columns past the width, rows past the tree
+      if (t < a.n_tok && i * 8 < a.hidden) {
+        o.x = f2bf(lo[j].x * gv[j][0][0]) | ((uint32_t)f2bf(lo[j].y * gv[j][0][1]) << 16);
+        o.y = f2bf(lo[j].z * gv[j][0][2]) | ((uint32_t)f2bf(lo[j].w * gv[j][0][3]) << 16);
+        o.z = f2bf(hi[j].x * gv[j][1][0]) | ((uint32_t)f2bf(hi[j].y * gv[j][1][1]) << 16);
+        o.w = f2bf(hi[j].z * gv[j][1][2]) | ((uint32_t)f2bf(hi[j].w * gv[j][1][3]) << 16);
+      }
+      *(uint4 *)(a.xa + packed_index(t, i * 8, a.xa_ks)) = o;
     }
   }
 }
@@ -323,9 +367,9 @@ hipError_t launch_pack_bf16(int kind, const sb_model_config &c, const void *src0
 hipError_t launch_embed_meta(const EmbedArgs &a, const TreeArg &tree, int blocks, int bf16,
                              hipStream_t s) {
   if (bf16)
-    hipLaunchKernelGGL(k_embed_meta<uint16_t>, dim3(blocks), dim3(256), 0, s, a, tree);
+    hipLaunchKernelGGL(k_embed_meta<uint16_t>, dim3(blocks), dim3(SB_MAX_ROWS), 0, s, a, tree);
   else
-    hipLaunchKernelGGL(k_embed_meta<float>, dim3(blocks), dim3(256), 0, s, a, tree);
+    hipLaunchKernelGGL(k_embed_meta<float>, dim3(blocks), dim3(SB_MAX_ROWS), 0, s, a, tree);
   return hipGetLastError();
 }
 

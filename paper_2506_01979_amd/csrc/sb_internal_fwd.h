@@ -80,6 +80,13 @@ struct EmbedArgs {
   Meta *meta;
   float2 *rope;  // [n_tok][head_dim/2] cos, sin
   int head_dim;
+  // bf16, nullable gain: the first layer's RMSNorm, bf16(h gain) packed into
+  // xa (xa_ks k-steps) and 1/rms per row into rs, as launch_rmsnorm_pack
+  const float *gain;
+  uint16_t *xa;
+  float *rs;
+  int xa_ks;
+  float eps;
   double theta[128];  // RoPE frequencies base^(-2j/d), j < head_dim/2
 };
 

@@ -226,7 +226,7 @@ def trace_summary(trace_dir: str, workload: str = WORKLOAD) -> str:
             j += 1
         if j >= len(rows) or "k_softmax_stats" not in rows[j]["Kernel_Name"]:
             continue
-        for tail in ("k_walk", "k_rollback"):
+        for tail in ("k_walk_clear", "k_walk", "k_rollback"):
             if j + 1 < len(rows) and tail in rows[j + 1]["Kernel_Name"]:
                 j += 1
         steps.append((i, j + 1))

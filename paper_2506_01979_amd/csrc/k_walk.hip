@@ -1,0 +1,686 @@
+// Branch Speculative Sampling at one node, and the accept/resample walk over
+// a token tree (Preliminaries, "Speculative Decoding"; Appendix, Algorithm 1
+// "Branch Speculative Sampling"):
+//   p(v)   = fl32(exp(fl32(fl32(l_v * fl32(1/T)) - zmax))) / total  (float64)
+//            or the one-hot at argmax when T = 0;
+//   accept = float64(u) < p~(x) / float64(q(x));
+//   reject : p~ <- max(0, p~ - q) / Z,  Z = sum max(0, p~ - q)   (float64),
+//            Z <= 0 keeps p~ and raises SB_FLAG_ZERO_RESIDUAL;
+//   draw   : C_v = running float64 sum of p~ in vocabulary order,
+//            y = min{v : C_v > u * W}, W the float64 total; a zero-mass
+//            token is never drawn.
+// The multiply-then-subtract of the logit transform must not be contracted
+// into an FMA: every operation rounds on its own, as the definition states.
+//
+// A walk is a chain of dependent vocabulary passes (each residual needs the
+// mass of the one before), so one compute unit's path to memory bounds it
+// when one workgroup does the passes: 12 us a pass at 32000 tokens, 30 at
+// 128256.  Here G workgroups of 256 threads share the vocabulary, 1024 to
+// 8192 consecutive tokens each, and keep their slice of p~ in registers from
+// pass to pass (nothing but q is read again).  All of them take the same
+// decisions from the same values; after a rejection each publishes its
+// slice's mass and the residual at the next candidate's token, and reads
+// everyone else's.  A draw looks up the slice masses it already has; only the
+// workgroup of the crossing slice searches its tokens.  Measured (the walk
+// with a rejection or two, one workgroup of 1024 threads -> these): 37 rows at
+// 128256 tokens 61 -> 11 us, 33 rows at 32000 tokens 23 -> 12 us, and 1.4 us
+// for the launch that clears the messages.
+#pragma clang fp contract(off)
+
+#include <limits.h>
+#include <math.h>
+
+#include "sb_device.h"
+#include "sb_internal.h"
+
+namespace sb {
+namespace {
+
+constexpr int kT = 256;  // threads of a workgroup
+constexpr int kNW = kT / 64;
+constexpr int kMaxG = 256;  // workgroups: one thread per slice mass
+// Ticks of the 100 MHz s_memrealtime counter a workgroup waits for the others
+// (50 ms; they arrive within microseconds unless the chip cannot hold them).
+constexpr unsigned long long kWaitTicks = 5000000ull;
+
+__device__ __forceinline__ double wave_sum(double v) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// Inclusive 64-lane scan.
+__device__ __forceinline__ double wave_scan(double x) {
+  const int lane = threadIdx.x & 63;
+  for (int o = 1; o < 64; o <<= 1) {
+    const double y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  return x;
+}
+
+// A target row's distribution; raw(v) is p before the factor scale().
+struct Row {
+  float inv_t, zmax;
+  double total;
+  int argmax, greedy;
+  __device__ __forceinline__ double raw(float l, int v) const {
+    if (greedy) return v == argmax ? 1.0 : 0.0;
+    const float z = l * inv_t;
+    return (double)expf(z - zmax);
+  }
+  __device__ __forceinline__ double scale() const { return greedy ? 1.0 : 1.0 / total; }
+  // p(v) divided exactly (the accept ratio of a tested token)
+  __device__ __forceinline__ double at(float l, int v) const {
+    if (greedy) return v == argmax ? 1.0 : 0.0;
+    const float z = l * inv_t;
+    return (double)expf(z - zmax) / total;
+  }
+};
+
+struct WalkShared {
+  double part[kNW], part2[kNW];
+  double z, cap;
+  int fail, first, last;
+};
+
+// Messages between the workgroups: per exchange and workgroup two words, the
+// complement of a float64's bits (a NaN as the canonical one), never 0; 0 is
+// "not there yet".  Three sets take turns: exchange k uses set k % 3, and its
+// publisher first clears its words of set (k + 1) % 3 -- they held exchange
+// k - 2, which everyone has read, since everyone published k - 1 after it --
+// and waits for that store, so who sees message k sees the cleared words.
+// Words move with device-scope relaxed stores and loads; the message is the
+// data, nothing else crosses workgroups.
+__device__ __forceinline__ unsigned long long encode(double v) {
+  if (v != v) return ~0x7ff8000000000000ull;
+  return ~__builtin_bit_cast(unsigned long long, v);
+}
+__device__ __forceinline__ double decode(unsigned long long w) {
+  return __builtin_bit_cast(double, ~w);
+}
+__device__ __forceinline__ void put(unsigned long long *p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long get(const unsigned long long *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Block-wide sums of v and c (every thread gets them).
+__device__ void block_sum2(double &v, double &c, WalkShared &sh) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  v = wave_sum(v);
+  c = wave_sum(c);
+  if (lane == 0) {
+    sh.part[w] = v;
+    sh.part2[w] = c;
+  }
+  __syncthreads();
+  v = (sh.part[0] + sh.part[1]) + (sh.part[2] + sh.part[3]);
+  c = (sh.part2[0] + sh.part2[1]) + (sh.part2[2] + sh.part2[3]);
+  __syncthreads();
+}
+
+// Block-wide inclusive scan of v in thread order.
+__device__ double block_scan(double v, WalkShared &sh) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double inc = wave_scan(v);
+  if (lane == 63) sh.part[w] = inc;
+  __syncthreads();
+  double off = 0.0;
+  for (int k = 0; k < w; ++k) off += sh.part[k];
+  __syncthreads();
+  return off + inc;
+}
+
+// The first thread whose inclusive sum inc passes thr with mass of its own;
+// when rounding leaves none, the last thread with mass; -1 without any mass.
+__device__ int block_cross(double mass, double inc, double thr, WalkShared &sh) {
+  if (threadIdx.x == 0) {
+    sh.first = INT_MAX;
+    sh.last = -1;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const unsigned long long hit = __ballot(mass > 0.0 && inc > thr), any = __ballot(mass > 0.0);
+  if (lane == 0) {
+    const int base = threadIdx.x;
+    if (hit) atomicMin(&sh.first, base + __ffsll((long long)hit) - 1);
+    if (any) atomicMax(&sh.last, base + 63 - __clzll((long long)any));
+  }
+  __syncthreads();
+  const int r = sh.first != INT_MAX ? sh.first : sh.last;
+  __syncthreads();
+  return r;
+}
+
+// The current distribution p~ = x scale of this workgroup's EPT kT tokens in
+// registers, thread t the EPT consecutive ones from v0.
+template <int EPT>
+struct Slices {
+  int vocab, vec4, G, g, v0;
+  unsigned long long *msg;  // [3][G][2]
+  int k;                    // exchanges so far
+  double x[EPT], scale, zdiv;
+  double mass;  // of workgroup threadIdx.x's slice, once have_mass
+  bool have_mass;
+
+  __device__ void init(int vocab_, int vec4_, unsigned long long *msg_) {
+    vocab = vocab_;
+    vec4 = vec4_;
+    G = gridDim.x;
+    g = blockIdx.x;
+    v0 = (g * kT + (int)threadIdx.x) * EPT;
+    msg = msg_;
+    k = 0;
+  }
+  __device__ __forceinline__ void load(const float *row, float (&f)[EPT]) const {
+    const __amdgpu_buffer_rsrc_t rs = uniform_rsrc(row, vocab * 4);
+    if (vec4) {
+#pragma unroll
+      for (int e = 0; e < EPT; e += 4) {
+        const f32x4 t = __builtin_bit_cast(
+            f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (v0 + e) * 4, 0, 0));
+        f[e] = t[0];
+        f[e + 1] = t[1];
+        f[e + 2] = t[2];
+        f[e + 3] = t[3];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < EPT; ++e)
+        f[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (v0 + e) * 4, 0, 0));
+    }
+  }
+  __device__ void set_row(const Row &r, const float *l) {
+    float f[EPT];
+    load(l, f);
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) x[e] = v0 + e < vocab ? r.raw(f[e], v0 + e) : 0.0;
+    scale = r.scale();
+    have_mass = false;
+  }
+  // Publishes this slice's sum and cap (only the thread that has one passes a
+  // cap) and reads everyone's: sh.z = the sum of the sums, sh.cap = the cap,
+  // own = workgroup threadIdx.x's sum.  False when a message stays out.
+  __device__ bool exchange(double sum, double cap, double &own, WalkShared &sh) {
+    block_sum2(sum, cap, sh);
+    if (threadIdx.x == 0) sh.fail = 0;
+    double s = threadIdx.x == 0 ? sum : 0.0, c = threadIdx.x == 0 ? cap : 0.0;
+    if (G > 1) {
+      unsigned long long *cur = msg + (size_t)(k % 3) * G * 2;
+      unsigned long long *nxt = msg + (size_t)((k + 1) % 3) * G * 2;
+      ++k;
+      if (threadIdx.x == 0) {
+        put(nxt + 2 * g, 0ull);
+        put(nxt + 2 * g + 1, 0ull);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        put(cur + 2 * g, encode(sum));
+        put(cur + 2 * g + 1, encode(cap));
+      }
+      __syncthreads();
+      s = c = 0.0;
+      if ((int)threadIdx.x < G) {
+        const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+        unsigned long long x = 0, y = 0;
+        for (;;) {
+          if (!x) x = get(cur + 2 * threadIdx.x);
+          if (!y) y = get(cur + 2 * threadIdx.x + 1);
+          if (x && y) break;
+          if (__builtin_amdgcn_s_memrealtime() - t0 > kWaitTicks) {
+            sh.fail = 1;
+            break;
+          }
+        }
+        s = x ? decode(x) : 0.0;
+        c = y ? decode(y) : 0.0;
+      }
+    }
+    own = s;
+    block_sum2(s, c, sh);
+    if (threadIdx.x == 0) {
+      sh.z = s;
+      sh.cap = c;
+    }
+    __syncthreads();
+    return sh.fail == 0;
+  }
+  // p~ <- max(0, p~ - q) / Z when Z > 0; sh.z = Z, sh.cap = the residual at
+  // token xcap (when xcap >= 0).
+  __device__ bool reject(const float *q, int xcap, WalkShared &sh) {
+    float f[EPT];
+    load(q, f);
+    double r[EPT], part = 0.0, cap = 0.0;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      r[e] = x[e] * scale - (double)f[e];
+      r[e] = r[e] > 0.0 && v0 + e < vocab ? r[e] : 0.0;
+      part += r[e];
+      cap = v0 + e == xcap ? r[e] : cap;
+    }
+    double own;
+    if (!exchange(part, cap, own, sh)) return false;
+    if (sh.z > 0.0) {
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) x[e] = r[e];
+      zdiv = sh.z;
+      scale = 1.0 / zdiv;
+      mass = own;
+      have_mass = true;
+    }
+    return true;
+  }
+  // sh.cap = the residual at token v.
+  __device__ bool fetch(int v, WalkShared &sh) {
+    double cap = 0.0, own;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) cap = v0 + e == v ? x[e] : cap;
+    return exchange(0.0, cap, own, sh);
+  }
+  __device__ bool draw(float u, int32_t *out, WalkShared &sh) {
+    double ts = 0.0;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) ts += x[e];
+    if (!have_mass && !exchange(ts, 0.0, mass, sh)) return false;
+    const double m = mass, inc = block_scan(m, sh);
+    if ((int)threadIdx.x == kT - 1) sh.z = inc;  // W: slices past G have none
+    __syncthreads();
+    const double thr = (double)u * sh.z;
+    const int cross = block_cross(m, inc, thr, sh);
+    if (cross < 0) {
+      if (g == 0 && threadIdx.x == 0) *out = vocab - 1;
+      return true;
+    }
+    if (cross != g) return true;
+    if ((int)threadIdx.x == cross) sh.cap = inc - m;
+    __syncthreads();
+    const double base = sh.cap, tinc = base + block_scan(ts, sh);
+    const int at = block_cross(ts, tinc, thr, sh);
+    if ((int)threadIdx.x == (at < 0 ? 0 : at)) {
+      int found = -1, last = v0;
+      double c = tinc - ts;
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        c += x[e];
+        if (x[e] > 0.0) {
+          last = v0 + e;
+          if (found < 0 && c > thr) found = v0 + e;
+        }
+      }
+      *out = found >= 0 ? found : last;
+    }
+    return true;
+  }
+};
+
+// The same by one workgroup with p~ in memory: after a message stayed out, and
+// for vocabularies past the slices' reach.
+struct InMemory {
+  int vocab;
+  double *arr;
+  Row row;
+  const float *l;
+  double scale, zdiv;
+  bool resid;
+  __device__ __forceinline__ double cur(int v) const { return resid ? arr[v] : row.raw(l[v], v); }
+  __device__ void set_row(const Row &r, const float *lrow) {
+    row = r;
+    l = lrow;
+    scale = r.scale();
+    resid = false;
+  }
+  __device__ bool reject(const float *q, int xcap, WalkShared &sh) {
+    // the residual is written over its input: keep the input when Z = 0 by
+    // summing first
+    double part = 0.0;
+    for (int v = threadIdx.x; v < vocab; v += kT) {
+      const double r = cur(v) * scale - (double)q[v];
+      part += r > 0.0 ? r : 0.0;
+    }
+    double none = 0.0;
+    block_sum2(part, none, sh);
+    if (threadIdx.x == 0) {
+      sh.z = part;
+      sh.cap = 0.0;
+    }
+    __syncthreads();
+    if (part > 0.0) {
+      for (int v = threadIdx.x; v < vocab; v += kT) {
+        double r = cur(v) * scale - (double)q[v];
+        r = r > 0.0 ? r : 0.0;
+        arr[v] = r;
+        if (v == xcap) sh.cap = r;
+      }
+      zdiv = part;
+      scale = 1.0 / zdiv;
+      resid = true;
+    }
+    __syncthreads();
+    return true;
+  }
+  __device__ bool fetch(int v, WalkShared &sh) {
+    if (threadIdx.x == 0) sh.cap = cur(v);
+    __syncthreads();
+    return true;
+  }
+  __device__ bool draw(float u, int32_t *out, WalkShared &sh) {
+    const int seg = (vocab + kT - 1) / kT, lo = threadIdx.x * seg, hi = min(vocab, lo + seg);
+    double ts = 0.0;
+    for (int v = lo; v < hi; ++v) ts += cur(v);
+    const double inc = block_scan(ts, sh);
+    if ((int)threadIdx.x == kT - 1) sh.z = inc;
+    __syncthreads();
+    const double thr = (double)u * sh.z;
+    const int at = block_cross(ts, inc, thr, sh);
+    if (at < 0) {
+      if (threadIdx.x == 0) *out = vocab - 1;
+    } else if ((int)threadIdx.x == at) {
+      int found = -1, last = lo;
+      double c = inc - ts;
+      for (int v = lo; v < hi; ++v) {
+        const double p = cur(v);
+        c += p;
+        if (p > 0.0) {
+          last = v;
+          if (found < 0 && c > thr) found = v;
+        }
+      }
+      *out = found >= 0 ? found : last;
+    }
+    return true;
+  }
+};
+
+// One call: the tree (select: a root with n - 1 children, row i of q and u
+// being candidate i - 1's) and its rows' values, in LDS.
+constexpr int kRows = SB_MAX_ROWS + 1;
+struct WalkRows {
+  int n;
+  int16_t par[kRows], path[kRows], kids[kRows];
+  int32_t tok[kRows], first[kRows];  // first: lowest-index child (INT_MAX: none)
+  float u[kRows], qx[kRows];         // qx: q of the row at its token
+  double px[kRows];                  // p of the row's parent at the row's token
+  sb_row_stats st[kRows];
+  unsigned long long kmask[kNW];
+  int node, plen, nk, decision, flags;
+};
+static_assert(SB_MAX_ROWS <= kT, "a walk's rows have a thread each");
+
+struct WalkIn {
+  int vocab, n, greedy;
+  float inv_t;
+  const int32_t *tokens;  // of row i: tokens[i - off]
+  const float *logits;
+  const sb_row_stats *stats;
+  const float *q, *u;  // rows i - off
+  int off;             // 0: walk; 1: select
+  int u_draw;          // index of the final draw's uniform
+};
+
+__device__ __forceinline__ Row row_of(const WalkIn &a, const sb_row_stats &s) {
+  return Row{a.inv_t, s.zmax, s.total, s.argmax, a.greedy};
+}
+
+// The accept test of row c against p~(its token) = px (thread 0).
+__device__ __forceinline__ bool accept(const WalkIn &a, const WalkRows &R, int c, double px, int *flags) {
+  const int x = R.tok[c];
+  double ratio = 0.0;  // a token id outside the vocabulary is rejected
+  if (x >= 0 && x < a.vocab) {
+    const double qx = (double)R.qx[c];
+    if (qx == 0.0) *flags |= SB_FLAG_QZERO;
+    ratio = px / qx;
+  } else {
+    *flags |= SB_FLAG_QZERO;
+  }
+  return (double)R.u[c] < ratio;
+}
+
+// The walk from the root.  Returns false when the distribution's owner gave up; else *out_tok has the final
+// token if this workgroup is the one to write it (`select`: only without an
+// acceptance).  *kept: the last accepted row (0: none), bonus: a leaf.
+template <class D>
+__device__ bool walk_run(D &d, const WalkIn &a, WalkRows &R, WalkShared &sh, bool select,
+                         int32_t *out_tok, int *nrej, int *bonus) {
+  for (;;) {
+    // While a node's first candidate is accepted against the node's own row,
+    // the tests read LDS only, and one thread walks them.  The failing one is
+    // taken again below, with its rejection.
+    if (threadIdx.x == 0 && !select) {
+      for (;;) {
+        const int c = R.first[R.node];
+        if (c == INT_MAX || !accept(a, R, c, R.px[c], &R.flags)) break;
+        R.path[R.plen++] = (int16_t)c;
+        R.node = c;
+      }
+    }
+    __syncthreads();
+    const int node = R.node;
+    // the children of `node` in index order, one thread per row (a selection's
+    // are all the other rows)
+    if (select) {
+      for (int j = threadIdx.x + 1; j < a.n; j += kT) R.kids[j - 1] = (int16_t)j;
+      if (threadIdx.x == 0) R.nk = a.n - 1;
+    } else {
+      const int j = threadIdx.x, w = j >> 6;
+      const unsigned long long m = __ballot(j > node && j < a.n && R.par[j] == node);
+      if ((j & 63) == 0) R.kmask[w] = m;
+      __syncthreads();
+      int before = __popcll(m & ((1ull << (j & 63)) - 1));
+      for (int v = 0; v < w; ++v) before += __popcll(R.kmask[v]);
+      if ((m >> (j & 63)) & 1) R.kids[before] = (int16_t)j;
+      if (j == kT - 1) R.nk = before + (int)((m >> 63) & 1);
+    }
+    __syncthreads();
+    const int nk = R.nk;
+    d.set_row(row_of(a, R.st[node]), a.logits + (size_t)node * a.vocab);
+    if (nk == 0) {
+      *bonus = 1;
+      return d.draw(a.u[a.u_draw], out_tok, sh);
+    }
+    int acc = -1;
+    bool resid = false;  // p~ is a residual
+    double px_at = 0.0;  // p~ at the next candidate's token, once it is
+    for (int i = 0; i < nk; ++i) {
+      const int c = R.kids[i];
+      if (threadIdx.x == 0) R.decision = accept(a, R, c, resid ? px_at : R.px[c], &R.flags);
+      __syncthreads();
+      const int ok = R.decision;
+      __syncthreads();
+      if (ok) {
+        acc = c;
+        break;
+      }
+      ++*nrej;
+      const int xn = i + 1 < nk ? R.tok[R.kids[i + 1]] : -1;
+      const int xcap = xn >= 0 && xn < a.vocab ? xn : -1;
+      if (!d.reject(a.q + (size_t)(c - a.off) * a.vocab, xcap, sh)) return false;
+      const double Z = sh.z;
+      if (Z > 0.0) {
+        resid = true;
+        px_at = sh.cap / Z;
+      } else {
+        if (threadIdx.x == 0) R.flags |= SB_FLAG_ZERO_RESIDUAL;
+        if (resid && xcap >= 0) {
+          __syncthreads();
+          if (!d.fetch(xcap, sh)) return false;
+          px_at = sh.cap / d.zdiv;
+        }
+      }
+      __syncthreads();
+    }
+    if (acc < 0) return d.draw(a.u[a.u_draw], out_tok, sh);
+    if (threadIdx.x == 0) {
+      R.path[R.plen++] = (int16_t)acc;
+      R.node = acc;
+    }
+    if (select) return true;
+    __syncthreads();
+  }
+}
+
+// The rows' values, before the first test.
+__device__ void walk_rows(const WalkIn &a, const TreeArg *tree, WalkRows &R) {
+  const int n = a.n;
+  for (int i = threadIdx.x; i < n; i += kT) {
+    R.par[i] = tree ? tree->parent[i] : (int16_t)(i == 0 ? -1 : 0);
+    if (tree || i == 0) R.st[i] = a.stats[i];
+    R.tok[i] = i >= a.off ? a.tokens[i - a.off] : -1;
+    R.u[i] = i >= a.off ? a.u[i - a.off] : 0.0f;
+    R.first[i] = INT_MAX;
+  }
+  if (threadIdx.x == 0) R.flags = 0;
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += kT) {
+    if ((tree || i == 0) && isnan(R.st[i].total)) atomicOr(&R.flags, SB_FLAG_NONFINITE);
+    if (i == 0) continue;
+    const int par = R.par[i], x = R.tok[i];
+    atomicMin(&R.first[par], i);
+    double px = 0.0;
+    float qx = 0.0f;
+    if (x >= 0 && x < a.vocab) {
+      px = row_of(a, R.st[par]).at(a.logits[(size_t)par * a.vocab + x], x);
+      qx = a.q[(size_t)(i - a.off) * a.vocab + x];
+    }
+    R.px[i] = px;
+    R.qx[i] = qx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    R.path[0] = 0;
+    R.node = 0;
+    R.plen = 1;
+  }
+  __syncthreads();
+}
+
+// EPT tokens per thread (0: one workgroup, p~ in memory).
+template <int EPT, bool SELECT>
+__global__ __launch_bounds__(kT) void k_walk(WalkIn a, TreeArg tree, int vec4,
+                                             sb_step_result *__restrict__ result,
+                                             int32_t *__restrict__ out,
+                                             unsigned long long *msg, double *arr) {
+  __shared__ WalkRows R;
+  __shared__ WalkShared sh;
+  walk_rows(a, SELECT ? nullptr : &tree, R);
+  int32_t *tok = SELECT ? out + 1 : &result->next_token;
+  int nrej = 0, bonus = 0;
+  bool done = false;
+  if constexpr (EPT > 0) {
+    Slices<EPT> d;
+    d.init(a.vocab, vec4, msg);
+    done = walk_run(d, a, R, sh, SELECT, tok, &nrej, &bonus);
+  }
+  if (blockIdx.x != 0) return;
+  if (!done) {
+    if (EPT > 0) walk_rows(a, SELECT ? nullptr : &tree, R);
+    nrej = bonus = 0;
+    InMemory d;
+    d.vocab = a.vocab;
+    d.arr = arr;
+    walk_run(d, a, R, sh, SELECT, tok, &nrej, &bonus);
+  }
+  __syncthreads();
+  if constexpr (SELECT) {
+    if (threadIdx.x == 0) {
+      const int acc = R.plen > 1 ? R.path[1] - 1 : -1;
+      out[0] = acc;
+      if (acc >= 0) out[1] = R.tok[acc + 1];
+      out[2] = R.flags;
+    }
+  } else {
+    if (threadIdx.x == 0) {
+      int branch = -1;
+      if (R.plen > 1) {
+        branch = 0;
+        for (int j = 1; j < R.path[1]; ++j)
+          if (R.par[j] == 0) ++branch;
+      }
+      result->n_accepted = R.plen - 1;
+      result->branch = branch;
+      result->path_len = R.plen;
+      result->flags = R.flags;
+      result->n_rejected = nrej;
+      result->bonus = bonus;
+      result->reserved = 0;
+    }
+    for (int j = threadIdx.x; j < SB_MAX_ROWS; j += kT)
+      result->path[j] = j < R.plen ? (int32_t)R.path[j] : -1;
+  }
+}
+
+__global__ __launch_bounds__(kT) void k_walk_clear(unsigned long long *p, int n) {
+  for (int i = threadIdx.x; i < n; i += kT) p[i] = 0;
+}
+
+// 1024 tokens a workgroup while 64 of them reach, then twice as many; past
+// 256 workgroups of 8192 one workgroup with p~ in memory.
+template <bool SELECT>
+hipError_t launch(const WalkIn &a, const TreeArg &tree, sb_step_result *result, int32_t *out,
+                  void *ws, hipStream_t s) {
+  double *arr = (double *)ws;  // 2 vocab float64: the residual, then the messages
+  unsigned long long *msg = (unsigned long long *)(arr + a.vocab);
+  const int vec4 = (a.vocab & 3) == 0;
+  int ept = 4;
+  while (ept < 32 && (a.vocab + kT * ept - 1) / (kT * ept) > 64) ept *= 2;
+  const int G = (a.vocab - 1) / (kT * ept) + 1;
+  if (G > kMaxG) {
+    hipLaunchKernelGGL((k_walk<0, SELECT>), dim3(1), dim3(kT), 0, s, a, tree, vec4, result, out, msg, arr);
+    return hipGetLastError();
+  }
+  if (G > 1) {
+    hipLaunchKernelGGL(k_walk_clear, dim3(1), dim3(kT), 0, s, msg, 3 * G * 2);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  switch (ept) {
+    case 4:
+      hipLaunchKernelGGL((k_walk<4, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, result, out, msg, arr);
+      break;
+    case 8:
+      hipLaunchKernelGGL((k_walk<8, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, result, out, msg, arr);
+      break;
+    case 16:
+      hipLaunchKernelGGL((k_walk<16, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, result, out, msg, arr);
+      break;
+    default:
+      hipLaunchKernelGGL((k_walk<32, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, result, out, msg, arr);
+  }
+  return hipGetLastError();
+}
+
+WalkIn walk_in(int vocab, int n, float temperature, const int32_t *tokens, const float *logits,
+               const sb_row_stats *stats, const float *q, const float *u) {
+  WalkIn a{};
+  a.vocab = vocab;
+  a.n = n;
+  a.greedy = temperature <= 0.0f ? 1 : 0;
+  a.inv_t = a.greedy ? 1.0f : 1.0f / temperature;
+  a.tokens = tokens;
+  a.logits = logits;
+  a.stats = stats;
+  a.q = q;
+  a.u = u;
+  return a;
+}
+
+}  // namespace
+
+size_t sample_ws_bytes(int vocab) { return (size_t)2 * (size_t)vocab * sizeof(double); }
+
+hipError_t launch_walk(int vocab, const TreeArg &tree, const int32_t *tokens, const float *logits,
+                       const sb_row_stats *stats, float temperature, const float *q,
+                       const float *u, sb_step_result *result, void *ws, hipStream_t s) {
+  return launch<false>(walk_in(vocab, tree.n, temperature, tokens, logits, stats, q, u), tree,
+                       result, nullptr, ws, s);
+}
+
+hipError_t launch_select(int vocab, const float *logits_row, const sb_row_stats *stats_row,
+                         float temperature, int n_cand, const int32_t *cand_tokens,
+                         const float *q, const float *u, int32_t *out, void *ws, hipStream_t s) {
+  WalkIn a = walk_in(vocab, n_cand + 1, temperature, cand_tokens, logits_row, stats_row, q, u);
+  a.off = 1;
+  a.u_draw = n_cand;
+  const TreeArg none{};
+  return launch<true>(a, none, nullptr, out, ws, s);
+}
+
+}  // namespace sb

@@ -14,7 +14,7 @@ struct TreeArg {
   int16_t parent[SB_MAX_ROWS];
 };
 
-// ---- sampling (k_sampling.hip) --------------------------------------------
+// ---- sampling (k_sampling.hip; the walk and the selection: k_walk.hip) -----
 // invalid (nullable): a device word; non-zero marks every row non-finite
 hipError_t launch_softmax_stats(int vocab, int n_rows, const float *logits, float temperature,
                                 sb_row_stats *stats, hipStream_t s,

@@ -203,6 +203,48 @@ def test_walk_parity(api, name, parents, vocab, T):
     assert checked >= cases - 2
 
 
+@pytest.mark.parametrize("vocab,T", [(1023, 1.0), (1024, 1.0), (1025, 0.8), (2047, 0.0), (65536, 1.0),
+                                     (65537, 0.7), (131073, 1.0), (270001, 1.0), (2097153, 1.0)])
+def test_select_slices(api, vocab, T):
+    """Selections whose candidates are mostly rejected, at the edges of the
+    vocabulary slices a workgroup holds (one workgroup, a slice of one token,
+    each slice width, a width not a multiple of 4, and the form in memory past
+    the slices' reach); one row is twice the distribution it tests, which
+    leaves a residual without mass."""
+    ws = torch.empty(api.sb_sample_workspace_bytes(vocab), dtype=torch.uint8, device="cuda")
+    out = torch.zeros(3, dtype=torch.int32, device="cuda")
+    checked, emitted = 0, 0
+    for seed in range(6 if vocab < 1000000 else 2):
+        say(f"select slices vocab={vocab} T={T} seed={seed}")
+        lg = synth.random_logits(1, vocab, 2.0, seed=500 + seed)[0]
+        p = sampling.target_probs(lg, T, sampling.row_stats(lg, T))
+        qr = synth.softmax_rows(synth.random_logits(1, vocab, 2.0, seed=600 + seed))[0]
+        qa = (0.4 * p + 0.6 * qr).astype(np.float32)
+        q = np.stack([qa, qr, qa, qr])
+        if seed % 2:
+            q[seed // 2 % 2] = (2.0 * p).astype(np.float32)
+        g = np.random.default_rng(seed)
+        toks = g.integers(0, vocab, 4).astype(np.int32)
+        toks[3] = np.argmax(p)
+        u = np.array([0.9, 0.97, 0.9, 0.5, synth.uniforms(1, seed=700 + seed)[0]], np.float32)
+        tr = []
+        res = sampling.branch_select(p, toks, q, u[:4], trace=tr)
+        if res.accepted is None:
+            want = (-1, sampling.draw(res.p_tilde, float(u[4]), tr, 4), res.flags)
+            emitted += 1
+        else:
+            want = (res.accepted, int(toks[res.accepted]), res.flags)
+        st = api.new_stats(1)
+        api.sb_softmax_stats(dev(lg[None]), T, st)
+        api.sb_select_branch(dev(lg), st, T, dev(toks), dev(q), dev(u), out, ws)
+        got = tuple(int(x) for x in out.cpu().numpy())
+        if decision_margin(tr, u) < TIE:
+            continue
+        assert got == want, (seed, got, want)
+        checked += 1
+    assert checked >= 1
+
+
 def test_walk_flags(api):
     vocab = 64
     parents = synth.branch_parents(2, 2)

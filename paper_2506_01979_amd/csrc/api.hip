@@ -53,7 +53,7 @@ struct Layout {
   // bf16
   size_t xa, act, q, part_o, part_ml, xn, ss, rs, pk_table, pk_sync;
   // f32
-  size_t fa, qkv, fq, fo, gu, fact;
+  size_t fq, fo, fact;
   size_t total;
   int np, n_chunks, pk_chunks, ks_h, ks_o, ks_f;
 };
@@ -73,7 +73,7 @@ Layout make_layout(const sb_model_config &c, int n_rows, int kv_len) {
   Layout L{};
   const int np = round_up(n_rows, 16);
   const int H = c.hidden, d = c.head_dim, F = c.ffn;
-  const int qd = c.n_heads * d, kvd = c.n_kv_heads * d;
+  const int qd = c.n_heads * d;
   const int G = c.n_heads / c.n_kv_heads;
   L.np = np;
   size_t off = 0;
@@ -111,11 +111,8 @@ Layout make_layout(const sb_model_config &c, int n_rows, int kv_len) {
     L.pk_table = take((size_t)c.n_layers * sizeof(PkLayer));
     L.pk_sync = take(sizeof(PkSync));
   } else {
-    L.fa = take((size_t)np * H * sizeof(float));
-    L.qkv = take((size_t)np * (qd + 2 * kvd) * sizeof(float));
     L.fq = take((size_t)np * qd * sizeof(float));
     L.fo = take((size_t)np * qd * sizeof(float));
-    L.gu = take((size_t)np * 2 * F * sizeof(float));
     L.fact = take((size_t)np * F * sizeof(float));
   }
   L.total = off;
@@ -441,15 +438,12 @@ sb_status forward_f32(sb_model *m, const sb_kv_cache *kv, int kv_len, const int3
                       sb_row_stats *stats, char *ws, const Layout &L, hipStream_t s) {
   const sb_model_config &c = m->cfg;
   const int H = c.hidden, d = c.head_dim, F = c.ffn;
-  const int qd = c.n_heads * d, kvd = c.n_kv_heads * d;
+  const int qd = c.n_heads * d;
   Meta *meta = (Meta *)(ws + L.meta);
   float2 *rope = (float2 *)(ws + L.rope);
   float *h = (float *)(ws + L.h);
-  float *a = (float *)(ws + L.fa);
-  float *qkv = (float *)(ws + L.qkv);
   float *q = (float *)(ws + L.fq);
   float *o = (float *)(ws + L.fo);
-  float *gu = (float *)(ws + L.gu);
   float *act = (float *)(ws + L.fact);
 
   EmbedArgs ea = embed_args(m, tokens, h, n, kv_len, meta, rope);
@@ -467,24 +461,38 @@ sb_status forward_f32(sb_model *m, const sb_kv_cache *kv, int kv_len, const int3
   aa.meta = meta;
   aa.scale = 1.0f / sqrtf((float)d);
 
+  F32Args fa{};
+  fa.n_tok = n;
+  fa.eps = c.rms_eps;
+  fa.n_heads = c.n_heads;
+  fa.n_kv = c.n_kv_heads;
+  fa.head_dim = d;
+  fa.cap = kv->capacity;
+  fa.kv_len = kv_len;
+  fa.rope = rope;
+  auto proj = [&](int mode, const float *x, const void *w, float *y, int rows, int cols,
+                  const float *gain) {
+    fa.X = x;
+    fa.W = (const float *)w;
+    fa.Y = y;
+    fa.M = rows;
+    fa.K = cols;
+    fa.gain = gain;
+    return launch_f32_proj(mode, fa, s);
+  };
   for (int l = 0; l < c.n_layers; ++l) {
     const sb_layer_weights &lw = m->layers[l];
-    float *kc = (float *)kv->k + l * layer_kv;
-    float *vc = (float *)kv->v + l * layer_kv;
-    SB_TRY(launch_f32_rmsnorm(h, lw.attn_norm, H, n, c.rms_eps, a, s));
-    SB_TRY(launch_f32_gemm(a, (const float *)lw.qkv, qkv, n, qd + 2 * kvd, H, qd + 2 * kvd, 0, s));
-    SB_TRY(launch_f32_rope_qkv(qkv, c, n, rope, q, kc, vc, kv->capacity, kv_len, s));
-    aa.kc = kc;
-    aa.vc = vc;
+    fa.kc = (float *)kv->k + l * layer_kv;
+    fa.vc = (float *)kv->v + l * layer_kv;
+    SB_TRY(proj(F32_QKV, h, lw.qkv, q, qd + 2 * c.n_kv_heads * d, H, lw.attn_norm));
+    aa.kc = fa.kc;
+    aa.vc = fa.vc;
     SB_TRY(launch_f32_attn(aa, o, s));
-    SB_TRY(launch_f32_gemm(o, (const float *)lw.o, h, n, H, qd, H, 1, s));
-    SB_TRY(launch_f32_rmsnorm(h, lw.mlp_norm, H, n, c.rms_eps, a, s));
-    SB_TRY(launch_f32_gemm(a, (const float *)lw.gate_up, gu, n, 2 * F, H, 2 * F, 0, s));
-    SB_TRY(launch_f32_swiglu(gu, n, F, act, s));
-    SB_TRY(launch_f32_gemm(act, (const float *)lw.down, h, n, H, F, H, 1, s));
+    SB_TRY(proj(F32_RESID, o, lw.o, h, H, qd, nullptr));
+    SB_TRY(proj(F32_SWIGLU, h, lw.gate_up, act, F, H, lw.mlp_norm));
+    SB_TRY(proj(F32_RESID, act, lw.down, h, H, F, nullptr));
   }
-  SB_TRY(launch_f32_rmsnorm(h, m->final_norm, H, n, c.rms_eps, a, s));
-  SB_TRY(launch_f32_gemm(a, (const float *)m->lm_head, logits, n, c.vocab, H, c.vocab, 0, s));
+  SB_TRY(proj(F32_PLAIN, h, m->lm_head, logits, c.vocab, H, m->final_norm));
   SB_TRY(launch_softmax_stats(c.vocab, n, logits, temperature, stats, s));
   return SB_OK;
 }

@@ -312,14 +312,25 @@ hipError_t launch_pk_table(const PkTableArgs &t, hipStream_t s);
 hipError_t launch_persist(const PkArgs &a, const void *kernel, int grid, hipStream_t s);
 
 // k_f32.hip
-hipError_t launch_f32_rmsnorm(const float *h, const float *g, int hidden, int n_tok, float eps,
-                              float *out, hipStream_t s);
-hipError_t launch_f32_gemm(const float *X, const float *W, float *Y, int n_tok, int M, int K,
-                           int ldy, int accumulate, hipStream_t s);
-hipError_t launch_f32_rope_qkv(const float *qkv, const sb_model_config &c, int n_tok,
-                               const float2 *rope, float *q, float *kc, float *vc, int cap,
-                               int kv_len, hipStream_t s);
+// A projection of a float32 model over rows of X [n_tok][K]:
+//   F32_QKV    X = the residual h; M = all rows of W; q after RoPE to Y
+//              [n_tok][n_heads][head_dim], k after RoPE and v to the caches;
+//   F32_RESID  Y [n_tok][M] += X W^T;
+//   F32_SWIGLU X = h; W = (gate; up), M rows each; Y [n_tok][M];
+//   F32_PLAIN  X = h; Y [n_tok][M] (the logits).
+// Those that read h apply the RMSNorm with gain.
+enum { F32_QKV = 0, F32_RESID = 1, F32_SWIGLU = 2, F32_PLAIN = 3 };
+struct F32Args {
+  const float *X, *W;
+  float *Y;
+  int n_tok, M, K;
+  const float *gain;
+  float eps;
+  int n_heads, n_kv, head_dim, cap, kv_len;
+  const float2 *rope;
+  float *kc, *vc;
+};
+hipError_t launch_f32_proj(int mode, const F32Args &a, hipStream_t s);
 hipError_t launch_f32_attn(const AttnArgs &a, float *out, hipStream_t s);
-hipError_t launch_f32_swiglu(const float *gu, int n_tok, int ffn, float *act, hipStream_t s);
 
 }  // namespace sb

@@ -183,6 +183,33 @@ def test_verify_forward_parity(api, sname, P, spec):
         assert np.array_equal(vp, np.asarray(Vp[:, :, :kv_len], np.float32))
 
 
+@pytest.mark.parametrize("hidden,heads,kv,d,ffn,vocab,P,n", [
+    (90, 2, 1, 48, 131, 37, 5, 17),     # columns not a multiple of 4, grouped queries
+    (64, 2, 2, 16, 66, 101, 1, 16),     # no prefix, one full row tile
+    (136, 1, 1, 256, 1100, 50, 70, 33),  # widest head, K over several rounds of the waves
+    (48, 4, 2, 32, 20, 16, 200, 1),     # one row
+])
+def test_float32_projection_edges(api, hidden, heads, kv, d, ffn, vocab, P, n):
+    """The float32 projections and attention at the edges of their tiles
+    (16 rows, 16 outputs, steps of 4 or 16 columns, 16 keys)."""
+    shape = synth.Shape(f"f32_{hidden}_{d}", 2, hidden, heads, kv, d, ffn, vocab, "f32")
+    say(f"float32 edges {shape.name} P={P} n={n}")
+    W = weights(shape)
+    parents = np.array([-1] + [(i - 1) // 2 for i in range(1, n)], np.int32)
+    ptoks = synth.prefix_tokens(vocab, P)
+    Kp = Vp = np.zeros((2, kv, 0, d))
+    if P > 1:
+        _, Kp, Vp = decoder.prefill(shape, W, ptoks[:-1], "f64")
+    toks = np.random.default_rng(n).integers(0, vocab, n).astype(np.int32)
+    ref, kt, vt = decoder.tree_forward(shape, W, Kp, Vp, P - 1, toks, parents, "f64")
+    m = model(api, shape)
+    got, k, v = gpu_forward(api, m, Kp, Vp, P - 1, toks, parents)
+    assert row_relerr(got, ref) < tol(shape)
+    kg, vg = m.read_kv(k, v, P - 1, n)
+    assert row_relerr(kg.reshape(-1, d), kt.reshape(-1, d)) < tol(shape) * 5
+    assert row_relerr(vg.reshape(-1, d), vt.reshape(-1, d)) < tol(shape) * 5
+
+
 @pytest.mark.parametrize("sname,n", [("ragged_bf16", n) for n in (65, 80, 81, 97, 112, 128, 144, 145, 160, 177,
                                                                   193, 209, 225, 241, 256)] +
                          [("widevocab_bf16", n) for n in (65, 128, 144, 145, 209, 256)])

@@ -189,7 +189,8 @@ void sb_model_destroy(sb_model *m);
 
 /* ---- the verify step ------------------------------------------------ */
 
-/* Workspace bytes sb_verify_forward needs for up to max_rows rows. */
+/* Workspace bytes sb_verify_forward needs for up to max_rows rows over a
+ * prefix of up to max_kv_len. */
 size_t sb_workspace_bytes(const sb_model *m, int32_t max_rows, int32_t max_kv_len);
 
 /* Target forward over the token tree (verification phase of Algorithm 2,
@@ -218,8 +219,8 @@ sb_status sb_verify_forward(sb_model *m, const sb_kv_cache *kv, int32_t kv_len,
  * the library's code is loaded on that device and held until the process
  * ends.  The call allocates nothing: its first call on a device (with that
  * device current) looks the array's address up once.
- * Errors: SB_ERR_CAPACITY when the step needs more workspace than the
- * array holds (sb_workspace_bytes(m, n_rows, kv_len) >
+ * Errors: SB_ERR_CAPACITY when the step itself needs more workspace than
+ * the array holds (never while sb_workspace_bytes(m, n_rows, kv_len) <=
  * SB_NOALLOC_SCRATCH_BYTES), before anything is enqueued; otherwise the
  * errors of sb_verify_forward.
  * Every call on one device shares that device's array: calls that overlap

@@ -69,7 +69,10 @@ int device_cus_host() {
   return cus;
 }
 
-Layout make_layout(const sb_model_config &c, int n_rows, int kv_len) {
+// Workspace layout of a call with n_rows rows; up_to: with room for every call
+// of at most n_rows rows (the attention's key ranges get fewer where a row more
+// takes another kernel or row block, so a smaller tree can have more partials).
+Layout make_layout(const sb_model_config &c, int n_rows, int kv_len, bool up_to = false) {
   Layout L{};
   const int np = round_up(n_rows, 16);
   const int H = c.hidden, d = c.head_dim, F = c.ffn;
@@ -92,10 +95,19 @@ Layout make_layout(const sb_model_config &c, int n_rows, int kv_len) {
     L.ks_o = pack_geom(c, SB_W_O).ks;
     L.ks_f = pack_geom(c, SB_W_DOWN).ks;
     const int ksx = L.ks_h > L.ks_o ? L.ks_h : L.ks_o;
-    L.n_chunks = attn_splits(c.n_kv_heads, c.head_dim, kv_len + n_rows, n_rows * G);
+    L.n_chunks = attn_plan(c.n_kv_heads, c.head_dim, kv_len + n_rows, n_rows * G).chunks;
     // key ranges of the persistent kernel's attention (one item per unit)
     L.pk_chunks = pk_attn_chunks(c.n_kv_heads, kv_len + n_rows, device_cus_host());
-    const int chunks = L.n_chunks > L.pk_chunks ? L.n_chunks : L.pk_chunks;
+    // partials: (key ranges) x (query rows) of a KV head
+    size_t parts = 0;
+    auto part_rows = [&](int rows) {
+      const int n = attn_plan(c.n_kv_heads, c.head_dim, kv_len + n_rows, rows).chunks;
+      const size_t p = (size_t)(n > L.pk_chunks ? n : L.pk_chunks) * rows;
+      if (p > parts) parts = p;
+    };
+    part_rows(n_rows * G);
+    if (up_to && n_rows * G > 16 * kAttnMaxRowTiles) part_rows(16 * kAttnMaxRowTiles / G * G);
+    for (int r = 16 * kAttnMaxWaves; up_to && r < n_rows * G; r += 16 * kAttnMaxWaves) part_rows(r / G * G);
     L.xa = take((size_t)np * ksx * 32 * 2);
     L.act = take((size_t)np * L.ks_f * 32 * 2);
     // the post-attention RMSNorm fused into the O projection: gated
@@ -105,8 +117,8 @@ Layout make_layout(const sb_model_config &c, int n_rows, int kv_len) {
     // 1/rms per row of the last RMSNorm kernel (its projection's scale)
     L.rs = take((size_t)np * sizeof(float));
     L.q = take((size_t)np * qd * 2);
-    L.part_o = take((size_t)c.n_kv_heads * chunks * n_rows * G * d * sizeof(float));
-    L.part_ml = take((size_t)c.n_kv_heads * chunks * n_rows * G * 2 * sizeof(float));
+    L.part_o = take(c.n_kv_heads * parts * d * sizeof(float));
+    L.part_ml = take(c.n_kv_heads * parts * 2 * sizeof(float));
     // the persistent kernel's layer table and barrier counters
     L.pk_table = take((size_t)c.n_layers * sizeof(PkLayer));
     L.pk_sync = take(sizeof(PkSync));
@@ -716,7 +728,7 @@ sb_status sb_timer_stop(sb_model *m, double *total_ms, int32_t *launches) {
 
 size_t sb_workspace_bytes(const sb_model *m, int32_t max_rows, int32_t max_kv_len) {
   if (!m || max_rows < 1 || max_rows > SB_MAX_ROWS || max_kv_len < 0) return 0;
-  return make_layout(m->cfg, max_rows, max_kv_len).total;
+  return make_layout(m->cfg, max_rows, max_kv_len, true).total;
 }
 
 sb_status sb_verify_forward(sb_model *m, const sb_kv_cache *kv, int32_t kv_len,

@@ -7,13 +7,13 @@
 // causal forward of that branch would see (Section "Branch Resampling").
 //
 // Flash-decoding split: the key range [0, kv_len + n_tok) of each KV head is
-// cut into n_chunks ranges of at most 2 NW 32-key steps (NW = head_dim / 16
-// waves per workgroup); a workgroup takes one range and one block of at
-// most 48 query rows of the KV head's group (with grouped queries a head's
-// group has n_tok G rows; the workgroups of one range sit on one XCD, so
-// its K and V come from HBM once and from that XCD's L2 after).  About one
-// workgroup per compute unit.  The workgroup reads its K rows and rows of
-// the transposed V cache straight into registers and scores its row block:
+// cut into n_chunks ranges, one workgroup each (and per block of query rows;
+// with grouped queries a KV head's group has n_tok G rows), and a merge kernel
+// combines the ranges.  Two kernels, by the group's rows:
+//
+// k_attn, at most 48 rows: the range (at most 2 NW steps of 32 keys, NW =
+// head_dim / 16 waves) is read once, straight into registers, and the waves
+// share the scoring by keys and the output by dimensions:
 //   1. wave w scores steps w and w + NW: S^T = K Q^T, masked, row max into
 //      LDS;
 //   2. after a barrier, the block max M of each row gives p = exp(s - M);
@@ -27,8 +27,27 @@
 //      element is finished by one wave, so the waves never merge
 //      accumulators.
 // K rows are fetched in a permuted order so that lane group lg of S^T holds
-// keys 8 lg .. 8 lg + 7, the layout P is stored and read back in.  The
-// workgroup writes an unnormalised partial (row max m, row sum l, sum p v)
+// keys 8 lg .. 8 lg + 7, the layout P is stored and read back in.
+//
+// k_attn_rows, more rows: the waves share the rows instead (a 16-row tile
+// each, every key and dimension), so each K and V byte is read once per
+// workgroup however many rows there are, and S^T lands in the layout P^T is
+// multiplied from: no probabilities in LDS, no maxima across waves.  The keys
+// go by in steps of 32 through a ring of four LDS buffers (direct-to-LDS loads
+// in operand order, two steps in flight while one is computed), with a running
+// softmax per row; a range can be long, so its partials are few.  Bound by the
+// loads (4 TB/s with the computation left out) and the softmax and product
+// arithmetic beside them.  Attention + merge, event-timed, against row blocks
+// of 48 in k_attn: 13B, 129 rows, prefix 8192 88 + 21 -> 63 + 8 us, prefix 512
+// 22 + 8 -> 16 + 9; 50 rows, prefix 8192 56 + 12 -> 47 + 7; 65 rows, prefix
+// 4096 37 + 11 -> 32 + 7, prefix 512 21 + 7 -> 12 + 7; 7B at 256 rows 28 + 9 ->
+// 25 + 9, at 65 rows and prefix 2048 21 + 8 -> 18 + 7; 70B at 33 rows (264 a KV
+// head) 27 + 10 -> 22 + 9, at 17 rows 26 + 7 -> 17 + 9, and level at 7 to 11
+// rows (56 to 88 a KV head), 13 + 7 -> 13.5 + 7.3.  Two tiles a wave (half the
+// LDS reads) was slower: 97 us at 129 rows, 5 waves on 4 SIMDs.  Starting the
+// ranges' steps at different places made no difference.
+//
+// A workgroup writes an unnormalised partial (row max m, row sum l, sum p v)
 // per query row; the merge kernel combines the ranges with the log-sum-exp
 // rule.
 #include <math.h>
@@ -97,13 +116,11 @@ __device__ __forceinline__ uint32_t visible8(const uint32_t *anc, int k0, int kv
   return vis;
 }
 
-// D: head_dim; RT: 16-row query tiles per row block; SW: 32-key steps per
+// D: head_dim; RT: 16-row query tiles; SW: 32-key steps per
 // wave (at most).  SW = 1 halves the keys, registers and LDS of a workgroup
 // so that two fit on a compute unit (launches of more workgroups than
 // compute units: one workgroup's scoring overlaps another's loads).
-// LOOP: the workgroup walks every row block of its key range (the launch
-// does not split the row blocks); otherwise it scores one.
-template <int D, int RT, int SW, bool LOOP>
+template <int D, int RT, int SW>
 __global__ __launch_bounds__(D * 4, SW == 1 ? 4 : 2) void k_attn(AttnArgs a) {
   constexpr int NW = D / 16;   // waves: one per 16 output dimensions
   constexpr int NT = NW * 64;
@@ -124,16 +141,11 @@ __global__ __launch_bounds__(D * 4, SW == 1 ? 4 : 2) void k_attn(AttnArgs a) {
   const int G = a.n_heads / a.n_kv;
   const float inv_g = 1.0f / (float)G;  // r / G = floor((r + 0.5) / G) for r < 2^20
   const int R = a.n_tok * G;
-  // Work unit (KV head g, key range split, row block), or (g, split) with
-  // every row block in turn when the launch does not split the row blocks
-  // (a.rb_split = 0).  Units are numbered XCD-major (workgroup b runs on
-  // XCD b % 8) with the row block fastest, so the workgroups that read the
-  // same key range sit on one XCD and share its L2.
-  const int n_rb = LOOP ? 1 : (R + RB - 1) / RB;
+  // Work unit (KV head g, key range split), numbered XCD-major (workgroup b
+  // runs on XCD b % 8).
   const int nb = gridDim.x;
   const int unit = (nb & 7) == 0 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
-  const int rb0 = (unit % n_rb) * RB;
-  const int g = unit / n_rb / a.n_chunks, split = unit / n_rb % a.n_chunks;
+  const int g = unit / a.n_chunks, split = unit % a.n_chunks;
   const int nkeys = a.kv_len + a.n_tok;
   const int n_steps = (nkeys + 31) >> 5;
   const int st0 = (n_steps * split) / a.n_chunks, st1 = (n_steps * (split + 1)) / a.n_chunks;
@@ -152,19 +164,19 @@ __global__ __launch_bounds__(D * 4, SW == 1 ? 4 : 2) void k_attn(AttnArgs a) {
   // exp(x * scale) = exp2(x * c): one FMA per score before the exp2
   const float c = a.scale * 1.44269504088896340736f;
 
-  // The staging loads of a row block (query rows, ancestor masks) go out
+  // The staging loads (query rows, ancestor masks) go out
   // before the cache reads: in-order completion lets the staging wait cover
   // only them.
   constexpr int QPT = (RB * (D / 8) + NT - 1) / NT;
   constexpr int APT = (RB * 8 + NT - 1) / NT;
   i32x4 qst[QPT];
   int ast[APT];
-  auto stage_loads = [&](int rb) {
+  {
 #pragma unroll
     for (int j = 0; j < QPT; ++j) {
       const int idx = threadIdx.x + j * NT;
       const int rr = idx / (D / 8), d0 = (idx % (D / 8)) * 8;
-      const int r = rb + rr;
+      const int r = rr;
       const int t = (int)(((float)r + 0.5f) * inv_g), hl = r - t * G;
       const int vo = (rr < RB && r < R) ? ((t * a.n_heads + g * G + hl) * D + d0) * 2 : qbytes;
       qst[j] = __builtin_amdgcn_raw_buffer_load_b128(qrs, vo, 0, 0);
@@ -173,13 +185,12 @@ __global__ __launch_bounds__(D * 4, SW == 1 ? 4 : 2) void k_attn(AttnArgs a) {
     for (int j = 0; j < APT; ++j) {
       const int idx = threadIdx.x + j * NT;
       const int rr = idx >> 3, wd = idx & 7;
-      const int r = rb + rr;
+      const int r = rr;
       const int t = (int)(((float)r + 0.5f) * inv_g);
       const int vo = (rr < RB && r < R) ? (t * 8 + wd) * 4 : abytes;
       ast[j] = __builtin_amdgcn_raw_buffer_load_b32(ars, vo, 0, 0);
     }
-  };
-  stage_loads(rb0);
+  }
   __builtin_amdgcn_sched_barrier(0);  // issue order: staging, K (V after scoring)
 
   // ---- the workgroup's cache reads, once, into registers.  Lanes whose
@@ -206,8 +217,7 @@ __global__ __launch_bounds__(D * 4, SW == 1 ? 4 : 2) void k_attn(AttnArgs a) {
   // requests delayed the keys the scoring waits for
   i32x4 vf[MS];
 
-  // one block of query rows (its staging loads already issued)
-  auto row_block = [&](int rb, bool first) {
+  {
     // ---- stage the block's query rows and ancestor masks
 #pragma unroll
     for (int j = 0; j < QPT; ++j) {
@@ -239,7 +249,7 @@ __global__ __launch_bounds__(D * 4, SW == 1 ? 4 : 2) void k_attn(AttnArgs a) {
           for (int i = 0; i < 2; ++i)
             sacc[i] = mfma16(__builtin_bit_cast(bf16x8, kf[u][i][ks]), as_bf16x8(qv), sacc[i]);
         }
-        // element e of sacc[i]: key k0 + 4 i + e, row rb + 16 rt + lr
+        // element e of sacc[i]: key k0 + 4 i + e, row 16 rt + lr
 #pragma unroll
         for (int j = 0; j < 8; ++j) sv[u][rt][j] = sacc[j >> 2][j & 3];
         if (sl >= nst) {
@@ -256,16 +266,14 @@ __global__ __launch_bounds__(D * 4, SW == 1 ? 4 : 2) void k_attn(AttnArgs a) {
       mx = max_x32(max_x16(mx));
       if (lg == 0) smax[w][rt * 16 + lr] = mx;
     }
-    if (first) {
-      __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < MS; ++j) {
-        const int key = (st0 + j) * 32 + 8 * lg;
-        const int vo = (j < nst && key < nkeys) ? ((16 * w + lr) * a.cap + key) * 2 : vbytes;
-        vf[j] = __builtin_amdgcn_raw_buffer_load_b128(vrs, vo, 0, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
+    for (int j = 0; j < MS; ++j) {
+      const int key = (st0 + j) * 32 + 8 * lg;
+      const int vo = (j < nst && key < nkeys) ? ((16 * w + lr) * a.cap + key) * 2 : vbytes;
+      vf[j] = __builtin_amdgcn_raw_buffer_load_b128(vrs, vo, 0, 0);
     }
+    __builtin_amdgcn_sched_barrier(0);
     lds_barrier();
 
     // ---- 2. probabilities against the block max, row sums
@@ -329,16 +337,15 @@ __global__ __launch_bounds__(D * 4, SW == 1 ? 4 : 2) void k_attn(AttnArgs a) {
         }
       }
     }
-    // lane holds dimensions 16 w + 4 lg .. + 3 of row rb + 16 rt + lr
+    // lane holds dimensions 16 w + 4 lg .. + 3 of row 16 rt + lr
     const size_t base = ((size_t)g * a.n_chunks + split) * R;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-      const int r = rb + rt * 16 + lr;
+      const int r = rt * 16 + lr;
       if (r < R) *(f32x4 *)&a.part_o[(base + r) * D + 16 * w + 4 * lg] = oacc[rt];
     }
     if (threadIdx.x < RB) {
-      const int rr = threadIdx.x;
-      const int r = rb + rr;
+      const int rr = threadIdx.x, r = rr;
       if (r < R) {
         float M = smax[0][rr], L = ssum[0][rr];
 #pragma unroll
@@ -350,17 +357,193 @@ __global__ __launch_bounds__(D * 4, SW == 1 ? 4 : 2) void k_attn(AttnArgs a) {
         *(float2 *)&a.part_ml[(base + r) * 2] = make_float2(M == -INFINITY ? M : M * a.scale, L);
       }
     }
-    lds_barrier();  // sp, sq, sanc, smax, ssum free for the next row block
-  };
-  // the first block straight after the cache reads (no loop around it, so
-  // the cache registers are not loop-carried and only the staging loads are
-  // waited for before scoring starts)
-  row_block(rb0, true);
-  if constexpr (LOOP)
-    for (int rb = RB; rb < R; rb += RB) {
-      stage_loads(rb);
-      row_block(rb, false);
+  }
+}
+
+// Direct-to-LDS load: 16 bytes per lane, 1 KB per wave instruction at dst.
+typedef __attribute__((address_space(3))) void lds_void;
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rs, char *dst, int vo, int so) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)dst, 16, vo, so, 0, 0);
+}
+
+// One 16-row query tile per wave, blockDim.x / 64 tiles per workgroup.  D:
+// head_dim; LPW: fragment loads per wave and step (the same for every wave, so
+// that its waits are constants: the ones past the step's fragments fill a
+// spare kilobyte with zeros).
+template <int D, int LPW>
+__global__ __launch_bounds__(64 * kAttnMaxWaves) void k_attn_rows(AttnArgs a, int n_rb) {
+  constexpr int KSD = D / 32;       // k-steps over head_dim (S)
+  constexpr int DT = D / 16;        // output tiles
+  constexpr int NF = 2 * KSD + DT;  // 1 KB fragments of a 32-key step: K, then V^T
+  constexpr int BB = (NF + 1) * 1024;
+  __shared__ __attribute__((aligned(16))) char b0[BB], b1[BB], b2[BB], b3[BB];
+  __shared__ __attribute__((aligned(16))) uint32_t sanc[SB_MAX_ROWS][8];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int G = a.n_heads / a.n_kv;
+  const int R = a.n_tok * G;
+  // Work unit (KV head, key range, row block), XCD-major, the row block
+  // fastest (the workgroups of one range share its reads through the L2).
+  const int xcd = blockIdx.x & 7, left = gridDim.x & 7;
+  const int unit = xcd * (gridDim.x >> 3) + (xcd < left ? xcd : left) + (blockIdx.x >> 3);
+  const int rb = unit % n_rb, g = unit / n_rb / a.n_chunks, split = unit / n_rb % a.n_chunks;
+  const int nkeys = a.kv_len + a.n_tok;
+  const int n_steps = (nkeys + 31) >> 5;
+  const int st0 = (n_steps * split) / a.n_chunks, st1 = (n_steps * (split + 1)) / a.n_chunks;
+  const int kbytes = a.cap * D * 2;  // one head's K (or V^T) block
+  const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)((const uint16_t *)a.kc + (size_t)g * a.cap * D), 0, kbytes, kBufferDword3);
+  const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)((const uint16_t *)a.vc + (size_t)g * D * a.cap), 0, kbytes, kBufferDword3);
+  const float c = a.scale * 1.44269504088896340736f;  // exp(x scale) = exp2(x c)
+
+  // A step's fragments in turn over the waves, each lane loading the 16 bytes
+  // it will read back: K key tile i, k-step ks (row rho of key tile i is key
+  // 8 (rho / 4) + 4 i + rho % 4, so that S^T's lane group lg holds keys
+  // 8 lg .. 8 lg + 7), then V^T dimension tile dt.  Keys past nkeys or the
+  // range read zero.
+  const int kslot = 8 * (lr >> 2) + (lr & 3);
+  auto issue = [&](int step, char *dst) {
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+      const int f = w + j * nw;  // uniform
+      const bool isk = f < 2 * KSD;
+      const int i = f / KSD, slot = step * 32 + kslot + 4 * i, key = step * 32 + 8 * lg;
+      const int kvo = (slot * D + 8 * lg) * 2 + (f - i * KSD) * 64;
+      const int vvo = ((16 * (f - 2 * KSD) + lr) * a.cap + key) * 2;
+      const bool in = step < st1 && f < NF && (isk ? slot : key) < nkeys;
+      load_to_lds(isk ? krs : vrs, dst + (f < NF ? f : NF) * 1024, in ? (isk ? kvo : vvo) : kbytes, 0);
     }
+  };
+  // The wave's query rows, as the B operand of S^T = K Q^T, and the ancestor
+  // masks (only where the range reaches past the prefix) go out before the
+  // cache reads: in-order completion lets their waits cover only them.
+  const int r = (rb * nw + w) * 16 + lr, t = r / G;
+  const int qbytes = a.n_tok * a.n_heads * D * 2;
+  const __amdgpu_buffer_rsrc_t qrs = __builtin_amdgcn_make_buffer_rsrc((void *)a.q, 0, qbytes, kBufferDword3);
+  const int tok = r < R ? t : 0;
+  i32x4 qf[KSD];
+#pragma unroll
+  for (int ks = 0; ks < KSD; ++ks)
+    qf[ks] = __builtin_amdgcn_raw_buffer_load_b128(
+        qrs, r < R ? ((t * a.n_heads + g * G + (r - t * G)) * D + 8 * lg) * 2 : qbytes, ks * 64, 0);
+  constexpr int APT = SB_MAX_ROWS * 2 / 256;  // 16-byte words per thread (4 waves or more)
+  const bool tree = st1 * 32 > a.kv_len;
+  i32x4 anc[APT];
+  if (tree) {
+    const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)a.meta->anc, 0, a.n_tok * 32, kBufferDword3);
+#pragma unroll
+    for (int j = 0; j < APT; ++j)
+      anc[j] = __builtin_amdgcn_raw_buffer_load_b128(ars, (threadIdx.x + j * blockDim.x) * 16, 0, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  issue(st0, b0);
+  issue(st0 + 1, b1);
+  issue(st0 + 2, b2);
+  __builtin_amdgcn_sched_barrier(0);
+  if (tree) {
+#pragma unroll
+    for (int j = 0; j < APT; ++j) {
+      const int i = threadIdx.x + j * blockDim.x;
+      if (i < a.n_tok * 2) *(i32x4 *)&sanc[i >> 1][4 * (i & 1)] = anc[j];
+    }
+  }
+  f32x4 o[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.0f;
+
+  auto compute = [&](int step, const char *src) {
+    const char *frag = src + lane * 16;
+    uint4 kf[2 * KSD], vf[DT];
+#pragma unroll
+    for (int f = 0; f < 2 * KSD; ++f) kf[f] = *(const uint4 *)(frag + f * 1024);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) vf[dt] = *(const uint4 *)(frag + (2 * KSD + dt) * 1024);
+    f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int ks = 0; ks < KSD; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        s[i] = mfma16(as_bf16x8(kf[i * KSD + ks]), __builtin_bit_cast(bf16x8, qf[ks]), s[i]);
+    const int k0 = step * 32 + 8 * lg;  // element e of s[i]: key k0 + 4 i + e
+    float p[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = s[j >> 2][j & 3];
+    if ((step + 1) * 32 > a.kv_len) {  // the step reaches past the prefix
+      const uint32_t vis = visible8(sanc[tok], k0, a.kv_len, nkeys);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) p[j] = (vis >> j) & 1u ? p[j] : -INFINITY;
+    }
+    float mx = fmaxf(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])),
+                     fmaxf(fmaxf(p[4], p[5]), fmaxf(p[6], p[7])));
+    mx = max_x32(max_x16(mx));
+    if (__ballot(mx > m)) {
+      // a larger maximum: the sums so far scale down (from -inf: to 0)
+      const float nm = fmaxf(m, mx);
+      const float f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m - nm) * c);
+      m = nm;
+      l *= f;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt] *= f;
+    }
+    const float mc = (m == -INFINITY ? 0.0f : m) * c;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      p[j] = __builtin_amdgcn_exp2f(fmaf(p[j], c, -mc));  // exp2(-inf) = 0 when masked
+      l += p[j];
+    }
+    uint32_t hw[4], lw[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      hw[e] = pack_bf16x2(p[2 * e], p[2 * e + 1]);
+      // p - bf16(p) is exact in float32
+      lw[e] = pack_bf16x2(p[2 * e] - __uint_as_float(hw[e] << 16),
+                          p[2 * e + 1] - __uint_as_float(hw[e] & 0xffff0000u));
+    }
+    const bf16x8 hi = as_bf16x8(make_uint4(hw[0], hw[1], hw[2], hw[3]));
+    const bf16x8 lo = as_bf16x8(make_uint4(lw[0], lw[1], lw[2], lw[3]));
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o[dt] = mfma16(as_bf16x8(vf[dt]), hi, o[dt]);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o[dt] = mfma16(as_bf16x8(vf[dt]), lo, o[dt]);
+  };
+  // Step `step` is there once every wave has waited for its own loads of it
+  // (two later steps may be in flight) and met the others; then the buffer of
+  // the step before is free for step + 3.
+  auto round = [&](int step, char *cur, char *nxt) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * LPW) : "memory");
+    issue(step + 3, nxt);
+    if ((step + 1) * 32 > nkeys && (nkeys & 7) != 0) {
+      // slots never written for this step count as zero in V too (0 x NaN)
+      const int key = step * 32 + 8 * lg, valid = nkeys - key;
+      if (valid > 0 && valid < 8)
+        for (int f = 2 * KSD + w; f < NF; f += nw) {
+          uint16_t *v = (uint16_t *)(cur + f * 1024 + lane * 16);
+          for (int e = valid; e < 8; ++e) v[e] = 0;
+        }
+      lds_barrier();
+    }
+    compute(step, cur);
+  };
+  for (int step = st0; step < st1; step += 4) {
+    round(step, b0, b3);
+    if (step + 1 < st1) round(step + 1, b1, b0);
+    if (step + 2 < st1) round(step + 2, b2, b1);
+    if (step + 3 < st1) round(step + 3, b3, b2);
+  }
+  // lane holds dimensions 16 dt + 4 lg .. + 3 of row r
+  const float sum = sum_x32(sum_x16(l));
+  if (r < R) {
+    const size_t at = ((size_t)g * a.n_chunks + split) * R + r;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) *(f32x4 *)&a.part_o[at * D + 16 * dt + 4 * lg] = o[dt];
+    // row max in units of the scaled score (s * scale)
+    if (lg == 0) *(float2 *)&a.part_ml[at * 2] = make_float2(m == -INFINITY ? m : m * a.scale, sum);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // loads into LDS still in flight
 }
 
 // Combines the key ranges of one (row t, query head) and writes the
@@ -463,16 +646,22 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, uint16_t *__rest
 // Threads per workgroup of the register merge: one wave, so that the few
 // thousand threads of a step spread over many compute units.
 constexpr int kMergeThreads = 64;
+constexpr int kMergeRanges = 8;  // ranges a lane of it merges
 
-// Merge for few key ranges (nc <= NCM): one thread per (row t, query head,
-// 8 output dimensions).  Every load -- the range statistics and the 8
-// dimensions of every range's partial output -- goes out before any use
-// (one memory round trip); the thread writes its 8 dimensions as one
-// 16-byte word of the packed operand layout of the O projection.
-template <int D, int NCM>
+// Merge for few key ranges (at most kMergeRanges H): H lanes per (row t,
+// query head, 8 output dimensions), each for kMergeRanges of the ranges; they
+// combine their sums by lane exchange.  Bound by latency: every load -- the
+// range statistics and the 8 dimensions of every range's partial output --
+// goes out before any use (one memory round trip).  8 ranges a lane rather
+// than 16 or 32, because the loads of a lane go out one after the other: 32
+// ranges take 7.3 us for 7 rows of 64 heads and 6.8 us for 33 of 12 with 8 a
+// lane, 8.2 and 7.7 us with 32 (7.9 and 7.2 us in k_attn_merge); 9 to 16
+// ranges are the same either way.  A lane writes 8 dimensions as one 16-byte
+// word of the packed operand layout of the O projection.
+template <int D, int H>
 __global__ __launch_bounds__(kMergeThreads) void k_attn_merge_reg(AttnArgs a,
                                                                   uint16_t *__restrict__ out, int ks) {
-  constexpr int TPP = D / 8;  // threads per (row, head)
+  constexpr int TPP = D / 8;  // parts of a (row, head); H lanes each
   const int nc = a.n_chunks;
   const int G = a.n_heads / a.n_kv;
   const int R = a.n_tok * G;
@@ -486,17 +675,17 @@ __global__ __launch_bounds__(kMergeThreads) void k_attn_merge_reg(AttnArgs a,
   const __amdgpu_buffer_rsrc_t ors =
       __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(a.part_o), 0, obytes, kBufferDword3);
   const int gid = blockIdx.x * kMergeThreads + threadIdx.x;
-  const int pair = gid / TPP, part = gid - pair * TPP;
+  const int pair = gid / (TPP * H), part = gid % TPP, c0 = gid / TPP % H * kMergeRanges;
   const bool live = pair < a.n_tok * a.n_heads;
   const int t = pair / a.n_heads, head = pair - t * a.n_heads;
   const int g = head / G;
   const int r = t * G + (head - g * G);
-  float2 st[NCM];
-  f32x4 lo[NCM], hi[NCM];
+  float2 st[kMergeRanges];
+  f32x4 lo[kMergeRanges], hi[kMergeRanges];
 #pragma unroll
-  for (int c = 0; c < NCM; ++c) {
-    const int row = (g * nc + c) * R + r;
-    const bool in = live && c < nc;
+  for (int c = 0; c < kMergeRanges; ++c) {
+    const int row = (g * nc + c0 + c) * R + r;
+    const bool in = live && c0 + c < nc;
     const int mo = in ? row * 8 : mbytes;
     const int oo = in ? (row * D + part * 8) * 4 : obytes;
     st[c].x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, mo, 0, 0));
@@ -506,19 +695,30 @@ __global__ __launch_bounds__(kMergeThreads) void k_attn_merge_reg(AttnArgs a,
   }
   __builtin_amdgcn_sched_barrier(0);  // all loads issued before any use
 #pragma unroll
-  for (int c = 0; c < NCM; ++c)
-    if (c >= nc) st[c].x = -INFINITY;
+  for (int c = 0; c < kMergeRanges; ++c)
+    if (c0 + c >= nc) st[c].x = -INFINITY;
   float M = st[0].x;
 #pragma unroll
-  for (int c = 1; c < NCM; ++c) M = fmaxf(M, st[c].x);
+  for (int c = 1; c < kMergeRanges; ++c) M = fmaxf(M, st[c].x);
+#pragma unroll
+  for (int o = TPP; o < TPP * H; o *= 2) M = fmaxf(M, __shfl_xor(M, o, 64));
   float L = 0.0f;
   f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int c = 0; c < NCM; ++c) {
+  for (int c = 0; c < kMergeRanges; ++c) {
     const float wgt = st[c].x == -INFINITY ? 0.0f : expf(st[c].x - M);
     L += wgt * st[c].y;
     o0 += wgt * lo[c];
     o1 += wgt * hi[c];
+  }
+#pragma unroll
+  for (int o = TPP; o < TPP * H; o *= 2) {
+    L += __shfl_xor(L, o, 64);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o0[e] += __shfl_xor(o0[e], o, 64);
+      o1[e] += __shfl_xor(o1[e], o, 64);
+    }
   }
   const float inv = 1.0f / L;
   uint4 pk;
@@ -526,7 +726,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_attn_merge_reg(AttnArgs a,
   pk.y = f2bf(o0[2] * inv) | ((uint32_t)f2bf(o0[3] * inv) << 16);
   pk.z = f2bf(o1[0] * inv) | ((uint32_t)f2bf(o1[1] * inv) << 16);
   pk.w = f2bf(o1[2] * inv) | ((uint32_t)f2bf(o1[3] * inv) << 16);
-  if (!live) return;
+  if (!live || c0 > 0) return;
   *(uint4 *)(out + packed_index(t, head * D + part * 8, ks)) = pk;
   // the last head's threads clear the row's padding columns (the GEMM
   // reads K in whole chunks)
@@ -538,113 +738,102 @@ __global__ __launch_bounds__(kMergeThreads) void k_attn_merge_reg(AttnArgs a,
 
 }  // namespace
 
-int attn_row_tiles(int rows) {
-  // row blocks of at most kAttnMaxRowTiles tiles, as even as the tile count
-  // allows
-  const int tiles = (rows + 15) / 16;
-  const int n_rb = (tiles + kAttnMaxRowTiles - 1) / kAttnMaxRowTiles;
-  return (tiles + n_rb - 1) / n_rb;
+AttnPlan attn_plan(int n_kv, int head_dim, int nkeys, int rows) {
+  AttnPlan p{};
+  const int tiles = (rows + 15) / 16, steps = (nkeys + 31) / 32;
+  if (tiles <= kAttnMaxRowTiles) {
+    // k_attn: at most SW head_dim / 16 steps per workgroup; two steps per wave
+    // while the workgroups fit the compute units at one each, beyond that one
+    // step, two workgroups per unit.  About kAttnTargetGroups workgroups in
+    // all while every one has kAttnMinSteps steps (shorter ranges cost more in
+    // partials and merging than the extra workgroups gain).
+    p.rt = tiles;
+    p.n_rb = 1;
+    const int ms2 = 2 * (head_dim / 16);
+    p.sw = (long long)n_kv * ((steps + ms2 - 1) / ms2) > kAttnCUs ? 1 : 2;
+    const int ms = p.sw * (head_dim / 16);
+    const int most = (steps + kAttnMinSteps - 1) / kAttnMinSteps;
+    int fill = (kAttnTargetGroups + n_kv - 1) / n_kv;
+    if (fill > most) fill = most;
+    p.chunks = (steps + ms - 1) / ms;
+    if (p.chunks < fill) p.chunks = fill;
+    return p;
+  }
+  // k_attn_rows: a tile per wave, as few row blocks as kAttnMaxWaves waves
+  // cover, and a workgroup per compute unit while each has two steps.  With
+  // two workgroups per unit for up to 6 waves, the partials and the merge
+  // take more than the second workgroup hides: 32 heads, 2048 keys, 65 rows
+  // 18 -> 23 us, 8 heads of 8, 4096 keys, 9 rows 14.5 -> 20.6 us.  Four steps
+  // at the least is slower on short prefixes (8 heads of 8, 300 keys, 17 rows
+  // 13.7 against 11.0 us), one step no faster and its merge 0.5 us slower.
+  p.rows = 1;
+  p.n_rb = (tiles + kAttnMaxWaves - 1) / kAttnMaxWaves;
+  p.waves = (tiles + p.n_rb - 1) / p.n_rb;
+  p.chunks = kAttnCUs / (n_kv * p.n_rb);
+  if (p.chunks > (steps + kAttnRowsMinSteps - 1) / kAttnRowsMinSteps)
+    p.chunks = (steps + kAttnRowsMinSteps - 1) / kAttnRowsMinSteps;
+  if (p.chunks < 1) p.chunks = 1;
+  return p;
 }
 
-bool attn_rb_split(int n_kv, int head_dim, int nkeys, int rows) {
-  // a workgroup per row block while the launch stays within 16 rounds of
-  // workgroups (the row blocks of one key range share its reads through
-  // the XCD's L2); beyond that each workgroup walks its row blocks and
-  // reads its keys once.  13B at prefix 8192: 65 rows 9.83 -> 9.35 ms per
-  // step, 129 rows 13.57 -> 13.36 against a limit of 4 rounds.
-  const int rt = attn_row_tiles(rows);
-  const int n_rb = (rows + 16 * rt - 1) / (16 * rt);
-  if (n_rb == 1) return true;
-  const int steps = (nkeys + 31) / 32;
-  const int ms2 = 2 * (head_dim / 16);
-  return (long long)n_kv * n_rb * ((steps + ms2 - 1) / ms2) <= 16LL * kAttnCUs;
-}
-
-int attn_steps_per_wave(int n_kv, int head_dim, int nkeys, int rows) {
-  // two steps per wave while the workgroups fit the compute units at one
-  // each; beyond that one step, two workgroups per unit
-  const int steps = (nkeys + 31) / 32;
-  const int rt = attn_row_tiles(rows);
-  const int n_rb = (rows + 16 * rt - 1) / (16 * rt);
-  // a workgroup that walks several row blocks keeps its keys in registers
-  // across them: two steps per wave (the one-step form spills there)
-  if (n_rb > 1 && !attn_rb_split(n_kv, head_dim, nkeys, rows)) return 2;
-  const int ms2 = 2 * (head_dim / 16);
-  const long long units2 = (long long)n_kv * n_rb * ((steps + ms2 - 1) / ms2);
-  return units2 > kAttnCUs ? 1 : 2;
-}
-
-int attn_splits(int n_kv, int head_dim, int nkeys, int rows) {
-  // at most SW head_dim / 16 steps of 32 keys per workgroup, and about
-  // kAttnTargetGroups workgroups in all (key ranges x row blocks) while
-  // every one has kAttnMinSteps steps (shorter ranges cost more in partials
-  // and merging than the extra workgroups gain)
-  const int steps = (nkeys + 31) / 32;
-  const int ms = attn_steps_per_wave(n_kv, head_dim, nkeys, rows) * (head_dim / 16);
-  const int n_rb = attn_rb_split(n_kv, head_dim, nkeys, rows)
-                       ? (rows + 16 * attn_row_tiles(rows) - 1) / (16 * attn_row_tiles(rows))
-                       : 1;
-  int sp = (steps + ms - 1) / ms;
-  int fill = (kAttnTargetGroups + n_kv * n_rb - 1) / (n_kv * n_rb);
-  const int most = (steps + kAttnMinSteps - 1) / kAttnMinSteps;
-  if (fill > most) fill = most;
-  if (sp < fill) sp = fill;
-  return sp < 1 ? 1 : sp;
-}
-
-template <int D, int SW, bool LOOP>
+template <int D, int SW>
 hipError_t launch_attn_dsw(const AttnArgs &a, int rt, const dim3 &grid, hipStream_t s) {
   const dim3 block(D * 4);
   switch (rt) {
-    case 1: hipLaunchKernelGGL((k_attn<D, 1, SW, LOOP>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_attn<D, 2, SW, LOOP>), grid, block, 0, s, a); break;
-    case 3: hipLaunchKernelGGL((k_attn<D, 3, SW, LOOP>), grid, block, 0, s, a); break;
+    case 1: hipLaunchKernelGGL((k_attn<D, 1, SW>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((k_attn<D, 2, SW>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((k_attn<D, 3, SW>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 template <int D>
-hipError_t launch_attn_d(const AttnArgs &a, hipStream_t s) {
-  const int rows = a.n_tok * (a.n_heads / a.n_kv);
-  const int nkeys = a.kv_len + a.n_tok;
-  const int rt = attn_row_tiles(rows);
-  const int n_rb = (rows + 16 * rt - 1) / (16 * rt);
-  const bool loop = n_rb > 1 && !attn_rb_split(a.n_kv, D, nkeys, rows);
-  const dim3 grid(a.n_kv * a.n_chunks * (loop ? 1 : n_rb));
-  const bool one = attn_steps_per_wave(a.n_kv, D, nkeys, rows) == 1;
-  if (loop)
-    return one ? launch_attn_dsw<D, 1, true>(a, rt, grid, s) : launch_attn_dsw<D, 2, true>(a, rt, grid, s);
-  return one ? launch_attn_dsw<D, 1, false>(a, rt, grid, s) : launch_attn_dsw<D, 2, false>(a, rt, grid, s);
+hipError_t launch_attn_d(const AttnArgs &a, const AttnPlan &p, hipStream_t s) {
+  const dim3 grid(a.n_kv * p.chunks * p.n_rb);
+  if (p.rows) {
+    const dim3 block(64 * p.waves);
+    const int lpw = ((D / 32) * 2 + D / 16 + p.waves - 1) / p.waves;  // at most 4: 4 waves or more
+    switch (lpw) {
+      case 1: hipLaunchKernelGGL((k_attn_rows<D, 1>), grid, block, 0, s, a, p.n_rb); break;
+      case 2: hipLaunchKernelGGL((k_attn_rows<D, 2>), grid, block, 0, s, a, p.n_rb); break;
+      case 3: hipLaunchKernelGGL((k_attn_rows<D, 3>), grid, block, 0, s, a, p.n_rb); break;
+      case 4: hipLaunchKernelGGL((k_attn_rows<D, 4>), grid, block, 0, s, a, p.n_rb); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
+  return p.sw == 1 ? launch_attn_dsw<D, 1>(a, p.rt, grid, s) : launch_attn_dsw<D, 2>(a, p.rt, grid, s);
 }
 
 hipError_t launch_attn_bf16(const AttnArgs &a, hipStream_t s) {
-  if (a.n_chunks != attn_splits(a.n_kv, a.head_dim, a.kv_len + a.n_tok,
-                                a.n_tok * (a.n_heads / a.n_kv)))
-    return hipErrorInvalidValue;
-  if (a.head_dim == 128) return launch_attn_d<128>(a, s);
-  if (a.head_dim == 64) return launch_attn_d<64>(a, s);
+  const AttnPlan p = attn_plan(a.n_kv, a.head_dim, a.kv_len + a.n_tok, a.n_tok * (a.n_heads / a.n_kv));
+  if (a.n_chunks != p.chunks) return hipErrorInvalidValue;
+  if (a.head_dim == 128) return launch_attn_d<128>(a, p, s);
+  if (a.head_dim == 64) return launch_attn_d<64>(a, p, s);
   return hipErrorInvalidValue;
+}
+
+template <int D, int H>
+hipError_t launch_merge_reg(const AttnArgs &a, uint16_t *out, int ks, hipStream_t s) {
+  const int threads = a.n_tok * a.n_heads * (D / 8) * H;
+  hipLaunchKernelGGL((k_attn_merge_reg<D, H>), dim3((threads + kMergeThreads - 1) / kMergeThreads),
+                     dim3(kMergeThreads), 0, s, a, out, ks);
+  return hipGetLastError();
 }
 
 hipError_t launch_attn_merge_bf16(const AttnArgs &a, uint16_t *out_packed, int out_ks,
                                   hipStream_t s) {
   if (a.n_chunks > 512) return hipErrorInvalidValue;
-  if (a.n_chunks <= 16 && (a.head_dim == 128 || a.head_dim == 64)) {
-    const int threads = a.n_tok * a.n_heads * (a.head_dim / 8);
-    const dim3 g((threads + kMergeThreads - 1) / kMergeThreads), b(kMergeThreads);
-    if (a.head_dim == 128) {
-      if (a.n_chunks <= 8)
-        hipLaunchKernelGGL((k_attn_merge_reg<128, 8>), g, b, 0, s, a, out_packed, out_ks);
-      else
-        hipLaunchKernelGGL((k_attn_merge_reg<128, 16>), g, b, 0, s, a, out_packed, out_ks);
-    } else {
-      if (a.n_chunks <= 8)
-        hipLaunchKernelGGL((k_attn_merge_reg<64, 8>), g, b, 0, s, a, out_packed, out_ks);
-      else
-        hipLaunchKernelGGL((k_attn_merge_reg<64, 16>), g, b, 0, s, a, out_packed, out_ks);
-    }
-    return hipGetLastError();
+  if (a.head_dim == 128 && a.n_chunks <= 4 * kMergeRanges) {
+    if (a.n_chunks <= kMergeRanges) return launch_merge_reg<128, 1>(a, out_packed, out_ks, s);
+    if (a.n_chunks <= 2 * kMergeRanges) return launch_merge_reg<128, 2>(a, out_packed, out_ks, s);
+    return launch_merge_reg<128, 4>(a, out_packed, out_ks, s);
+  }
+  if (a.head_dim == 64 && a.n_chunks <= 4 * kMergeRanges) {
+    if (a.n_chunks <= kMergeRanges) return launch_merge_reg<64, 1>(a, out_packed, out_ks, s);
+    if (a.n_chunks <= 2 * kMergeRanges) return launch_merge_reg<64, 2>(a, out_packed, out_ks, s);
+    return launch_merge_reg<64, 4>(a, out_packed, out_ks, s);
   }
   dim3 grid(a.n_tok, a.n_heads);
   if (a.head_dim == 128)

@@ -148,7 +148,7 @@ struct AttnArgs {
   const void *q;        // bf16 or f32 [rows][n_heads][d]
   const void *kc, *vc;  // this layer's cache [n_kv][cap][d]
   int cap, kv_len, n_tok, n_heads, n_kv, head_dim;
-  int n_chunks;     // key ranges per KV head (attn_splits)
+  int n_chunks;     // key ranges per KV head (attn_plan)
   const Meta *meta;
   float scale;
   float *part_o;   // [n_kv][n_chunks][R][d]
@@ -232,17 +232,19 @@ extern thread_local LaunchEvents g_launch_events;
 bool resid_norm_fusable(int tiles, int ks, int n_tok, int *groups);
 
 // k_attn.hip
-// Key ranges per KV head: about kAttnTargetGroups workgroups in all, one per
-// (KV head, key range, block of at most 16 kAttnMaxRowTiles query rows of
-// the head's group).
+// Launch shape for `rows` query rows per KV head: k_attn (rt row tiles, sw
+// steps per wave) or k_attn_rows (rows = 1: a row tile per wave, n_rb row
+// blocks), and the key ranges per KV head.
 constexpr int kAttnTargetGroups = 256;
 constexpr int kAttnMinSteps = 4;
-constexpr int kAttnMaxRowTiles = 3;  // 48-row blocks (64: 70B step 0.36 ms slower)
+constexpr int kAttnRowsMinSteps = 2;
+constexpr int kAttnMaxRowTiles = 3;  // of k_attn
+constexpr int kAttnMaxWaves = 12;    // of a k_attn_rows workgroup
 constexpr int kAttnCUs = 256;  // compute units the launch shape is planned for (MI355X)
-int attn_row_tiles(int rows);
-int attn_steps_per_wave(int n_kv, int head_dim, int nkeys, int rows);
-bool attn_rb_split(int n_kv, int head_dim, int nkeys, int rows);
-int attn_splits(int n_kv, int head_dim, int nkeys, int rows);
+struct AttnPlan {
+  int rows, rt, sw, waves, n_rb, chunks;
+};
+AttnPlan attn_plan(int n_kv, int head_dim, int nkeys, int rows);
 hipError_t launch_attn_bf16(const AttnArgs &a, hipStream_t s);
 hipError_t launch_attn_merge_bf16(const AttnArgs &a, uint16_t *out_packed, int out_ks,
                                   hipStream_t s);

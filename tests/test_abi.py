@@ -256,6 +256,22 @@ def test_noalloc_scratch_covers_the_stated_steps(api, shape, rows, prefixes):
         api.lib.sb_model_destroy(h)
 
 
+@pytest.mark.parametrize("shape", ["llama13b", "llama70b", "draft68m"])
+def test_workspace_serves_smaller_trees(api, shape):
+    """Workspace bytes never fall as rows or prefix grow: one sized for the
+    largest tree serves every smaller one (49 rows take fewer key ranges than
+    48, 193 fewer than 192)."""
+    h, _w = _fake_model(api, shape, 1)
+    try:
+        least = 0
+        for P in (0, 37, 740, 4095, 16000):
+            sizes = [api.lib.sb_workspace_bytes(h, n, P) for n in range(1, 257)]
+            assert sizes == sorted(sizes) and sizes[0] >= least
+            least = sizes[0]
+    finally:
+        api.lib.sb_model_destroy(h)
+
+
 def test_round_host_validation_without_device(api):
     """sb_round_finish and sb_spec_round reject bad arguments before any
     launch; the round's workspace size is host arithmetic."""

@@ -234,6 +234,40 @@ def test_wide_gemm_token_tiles(api, sname, n):
     assert row_relerr(vg.reshape(-1, shape.head_dim), vt.reshape(-1, shape.head_dim)) < tol(shape) * 5
 
 
+@pytest.mark.parametrize("heads,kv,d,P,n", [
+    # rows per KV head at the edges of a wave's 16-row tile: 48 rows (the
+    # last count of the other kernel), 49 and 64 (4 tiles), 65, 96, 97, 113
+    (4, 4, 128, 100, 48), (4, 4, 128, 100, 49), (4, 4, 64, 100, 64), (4, 4, 128, 100, 65),
+    (4, 4, 64, 101, 96), (4, 4, 128, 103, 97), (2, 2, 64, 31, 113),
+    # 192 rows (one row block of 12 tiles), 193 (two blocks of 7 and 6),
+    # grouped queries that share a tile: 50, 392 and 512 rows a KV head
+    (2, 2, 128, 33, 192), (2, 2, 64, 33, 193), (10, 2, 64, 257, 10), (8, 1, 128, 40, 49), (4, 2, 128, 7, 256),
+    # tree rows only; a last step of one key; one step per range and one in all
+    (4, 4, 128, 0, 49), (4, 4, 64, 0, 97), (4, 4, 128, 112, 49), (64, 64, 64, 64, 64), (16, 1, 128, 1, 4),
+    # 8, 9, 16, 17, 32, 33 and 64 key ranges for the merge (a lane's share of
+    # them and one more; 33 and 64 are the other merge kernel)
+    (4, 4, 64, 460, 50), (4, 4, 128, 500, 50), (4, 4, 64, 970, 50), (4, 4, 128, 1030, 50), (8, 8, 64, 2500, 50),
+    (4, 4, 128, 2060, 50), (4, 4, 64, 4100, 50)])
+def test_attention_row_tiles(api, heads, kv, d, P, n):
+    """k_attn_rows (a row tile per wave) and the merge at the edges of their
+    tiles, row blocks, key ranges and lanes; the bound of the other bf16
+    forwards (same rounding points)."""
+    shape = synth.Shape(f"attn{heads}x{kv}x{d}", 2, 256, heads, kv, d, 264, 500, "bf16")
+    say(f"attention rows heads={heads}/{kv} d={d} P={P} n={n}")
+    parents = np.array([-1] + [(i - 1) // 2 for i in range(1, n)], np.int32)  # own paths of 1 .. 8 rows
+    toks = np.random.default_rng(P + n).integers(0, shape.vocab, n).astype(np.int32)
+    g = np.random.default_rng(P)
+    dims = (shape.n_layers, kv, P, d)
+    Kp, Vp = (decoder.round_bf16(g.standard_normal(dims).astype(np.float32)) for _ in range(2))
+    ref, kt, vt = decoder.tree_forward(shape, weights(shape), Kp, Vp, P, toks, parents, "bf16")
+    m = model(api, shape)
+    got, k, v = gpu_forward(api, m, Kp, Vp, P, toks, parents)
+    assert row_relerr(got, ref) < tol(shape)
+    kg, vg = m.read_kv(k, v, P, n)
+    assert row_relerr(kg.reshape(-1, d), kt.reshape(-1, d)) < tol(shape) * 5
+    assert row_relerr(vg.reshape(-1, d), vt.reshape(-1, d)) < tol(shape) * 5
+
+
 @pytest.mark.parametrize("sname,kind,T", [
     ("small_bf16", "ties", 1.0), ("small_bf16", "ties", 0.0), ("ragged_bf16", "ties", 0.7),
     ("small_bf16", "nonfinite", 1.0), ("small_bf16", "nonfinite", 0.0),

@@ -29,6 +29,8 @@ struct sb_model {
   float *tap = nullptr;
   int tap_k = 0, tap_rows = 0;
   int fwd_mode = SB_FWD_AUTO;  // sb_model_set_forward
+  // RoPE frequencies theta_j = base^(-2j/d), evaluated once in float64
+  double theta[128] = {};
 };
 
 // Scratch memory of sb_verify_forward_noalloc: the forward's workspace as a
@@ -178,8 +180,7 @@ inline sb_status hip_status(hipError_t e) { return e == hipSuccess ? SB_OK : SB_
 
 size_t elem_bytes(const sb_model_config &c) { return c.dtype == SB_BF16 ? 2 : 4; }
 
-// Embedding / metadata arguments, with the RoPE frequencies theta_j =
-// base^(-2j/d) evaluated once on the host in float64.
+// Embedding / metadata arguments.
 EmbedArgs embed_args(const sb_model *m, const int32_t *tokens, float *h, int n, int kv_len,
                      Meta *meta, float2 *rope) {
   const sb_model_config &c = m->cfg;
@@ -194,8 +195,7 @@ EmbedArgs embed_args(const sb_model *m, const int32_t *tokens, float *h, int n, 
   ea.meta = meta;
   ea.rope = rope;
   ea.head_dim = c.head_dim;
-  for (int j = 0; j < c.head_dim / 2 && j < 128; ++j)
-    ea.theta[j] = pow((double)c.rope_theta, -2.0 * (double)j / (double)c.head_dim);
+  memcpy(ea.theta, m->theta, sizeof(ea.theta));
   return ea;
 }
 
@@ -661,6 +661,8 @@ sb_status sb_model_create(const sb_model_config *cfg, const sb_model_weights *w,
   sb_model *m = new (std::nothrow) sb_model;
   if (!m) return SB_ERR_INVALID_ARG;
   m->cfg = *cfg;
+  for (int j = 0; j < cfg->head_dim / 2 && j < 128; ++j)
+    m->theta[j] = pow((double)cfg->rope_theta, -2.0 * (double)j / (double)cfg->head_dim);
   m->layers.assign(w->layers, w->layers + cfg->n_layers);
   m->embed = w->embed;
   m->final_norm = w->final_norm;

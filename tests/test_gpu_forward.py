@@ -234,6 +234,22 @@ def test_wide_gemm_token_tiles(api, sname, n):
     assert row_relerr(vg.reshape(-1, shape.head_dim), vt.reshape(-1, shape.head_dim)) < tol(shape) * 5
 
 
+@pytest.mark.parametrize("hidden,ffn,n", [(4096, 1032, 17), (4112, 1032, 17), (5120, 1032, 1), (5120, 1032, 33),
+                                          (5120, 1032, 64), (5120, 264, 33), (6152, 1032, 33), (8192, 1032, 17)])
+def test_down_projection_splits(api, hidden, ffn, n):
+    """The down projection's K split: 256 and 257 output tiles, 320 (quarters:
+    5 tiles a workgroup), 385 with a ragged last tile, 512 (halves), and an
+    inner width with fewer chunks than four."""
+    shape = synth.Shape(f"down{hidden}x{ffn}", 1, hidden, 4, 2, 64, ffn, 300, "bf16")
+    say(f"down projection hidden={hidden} ffn={ffn} n={n}")
+    parents = np.array([-1] + [(i - 1) // 2 for i in range(1, n)], np.int32)
+    toks = np.random.default_rng(n).integers(0, shape.vocab, n).astype(np.int32)
+    empty = np.zeros((1, 2, 0, 64))
+    ref, _, _ = decoder.tree_forward(shape, weights(shape), empty, empty, 0, toks, parents, "bf16")
+    got, _, _ = gpu_forward(api, model(api, shape), None, None, 0, toks, parents)
+    assert row_relerr(got, ref) < tol(shape)
+
+
 @pytest.mark.parametrize("heads,kv,d,P,n", [
     # rows per KV head at the edges of a wave's 16-row tile: 48 rows (the
     # last count of the other kernel), 49 and 64 (4 tiles), 65, 96, 97, 113

@@ -9,9 +9,7 @@
 namespace sb {
 namespace {
 
-constexpr int kL1Threads = 512;
-constexpr int kL1Batch = 10;  // 16-byte loads of W1 in flight per thread
-constexpr int kTailThreads = 512;
+constexpr int kL1Threads = 256;
 
 // The row and token the features come from: the last row of the walk's
 // path and its next token; false when the result names no usable pair.
@@ -29,48 +27,30 @@ __device__ __forceinline__ bool hrad_source(const HradArgs &a, int *row, int *to
 // One workgroup per unit j of the first layer: y1[j] = ReLU(W1[j] . z + b1[j]),
 // z = (tap 0 .. tap k-1 of the row, the token's embedding); a thread takes 4
 // consecutive inputs per step (hidden is a multiple of 8, so 4 never straddle
-// two parts of z).  Bound by W1 from memory (21 MB at hidden 4096 and 4 taps):
-// the weights of kL1Batch steps go out before the row and the token, a chain
-// of three dependent reads, are looked up.  10.6 -> 6.9 us.
+// two parts of z).
 __global__ __launch_bounds__(kL1Threads) void k_hrad_l1(HradArgs a) {
   __shared__ float red[kL1Threads / 64];
   const int j = blockIdx.x;
-  const int H = a.hidden;
-  const int din = (a.k + 1) * H;
-  const __amdgpu_buffer_rsrc_t wrs = uniform_rsrc(a.w1 + (size_t)j * din, din * 4);
-  f32x4 wv[kL1Batch];
-  auto load_w = [&](int i0) {
-#pragma unroll
-    for (int b = 0; b < kL1Batch; ++b)
-      wv[b] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                            wrs, (i0 + b * kL1Threads * 4) * 4, 0, 0));
-  };
-  const int first = (int)threadIdx.x * 4;
-  load_w(first);
-  __builtin_amdgcn_sched_barrier(0);
   int r = 0, y = 0;
   const bool ok = hrad_source(a, &r, &y);
+  const int H = a.hidden;
+  const int din = (a.k + 1) * H;
+  const float *wr = a.w1 + (size_t)j * din;
   float acc = 0.0f;
   if (ok) {
-    for (int i0 = first; i0 < din; i0 += kL1Batch * kL1Threads * 4) {
-      if (i0 != first) load_w(i0);
-#pragma unroll
-      for (int b = 0; b < kL1Batch; ++b) {
-        const int i = i0 + b * kL1Threads * 4;
-        f32x4 zv = {0.f, 0.f, 0.f, 0.f};
-        if (i < din) {
-          const int k = i / H, d = i - k * H;
-          if (k < a.k) {
-            zv = *(const f32x4 *)(a.taps + ((size_t)k * a.max_rows + r) * H + d);
-          } else {
-            const uint2 e = *(const uint2 *)(a.embed + (size_t)y * H + d);
-            zv = f32x4{bf2f((uint16_t)(e.x & 0xffff)), bf2f((uint16_t)(e.x >> 16)),
-                       bf2f((uint16_t)(e.y & 0xffff)), bf2f((uint16_t)(e.y >> 16))};
-          }
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc += wv[b][c] * zv[c];
+    for (int i = threadIdx.x * 4; i < din; i += kL1Threads * 4) {
+      const f32x4 wv = *(const f32x4 *)(wr + i);
+      const int k = i / H, d = i - k * H;
+      f32x4 zv;
+      if (k < a.k) {
+        zv = *(const f32x4 *)(a.taps + ((size_t)k * a.max_rows + r) * H + d);
+      } else {
+        const uint2 e = *(const uint2 *)(a.embed + (size_t)y * H + d);
+        zv = f32x4{bf2f((uint16_t)(e.x & 0xffff)), bf2f((uint16_t)(e.x >> 16)),
+                   bf2f((uint16_t)(e.y & 0xffff)), bf2f((uint16_t)(e.y >> 16))};
       }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc += wv[c] * zv[c];
     }
   }
   for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
@@ -84,52 +64,32 @@ __global__ __launch_bounds__(kL1Threads) void k_hrad_l1(HradArgs a) {
   }
 }
 
-// The 64-unit layer, then the 3 logits and their argmax (lowest index on
-// ties).  Bound by latency: 8 lanes per unit read its row of W2 as 16-byte
-// pieces, every load of the kernel out before the first use; one thread per
-// unit took 256 dependent steps (8.9 -> 4.4 us).
-__global__ __launch_bounds__(kTailThreads) void k_hrad_tail(HradArgs a) {
-  constexpr int LPU = kTailThreads / SB_HRAD_H2;      // lanes per unit
-  constexpr int STEPS = SB_HRAD_H1 / (4 * LPU);       // 16-byte pieces per lane
-  static_assert(LPU * SB_HRAD_H2 == kTailThreads && STEPS * 4 * LPU == SB_HRAD_H1, "whole pieces");
-  __shared__ __attribute__((aligned(16))) float y1[SB_HRAD_H1];
-  __shared__ float y2[SB_HRAD_H2], lg[SB_HRAD_CLASSES];
-  const int m = threadIdx.x / LPU, part = threadIdx.x % LPU;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const __amdgpu_buffer_rsrc_t wrs = uniform_rsrc(a.w2, SB_HRAD_H2 * SB_HRAD_H1 * 4);
-  f32x4 wv[STEPS];
-#pragma unroll
-  for (int i = 0; i < STEPS; ++i)
-    wv[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                          wrs, (m * SB_HRAD_H1 + (i * LPU + part) * 4) * 4, 0, 0));
-  const float b2 = a.b2[m];
-  const float w3 = w < SB_HRAD_CLASSES ? a.w3[(size_t)w * SB_HRAD_H2 + lane] : 0.0f;
-  const float b3 = w < SB_HRAD_CLASSES ? a.b3[w] : 0.0f;
-  if (threadIdx.x < SB_HRAD_H1) y1[threadIdx.x] = a.y1[threadIdx.x];
+// The 64-unit layer (thread m computes unit m), then the 3 logits and their
+// argmax (lowest index on ties) by thread 0.
+__global__ __launch_bounds__(SB_HRAD_H2) void k_hrad_tail(HradArgs a) {
+  __shared__ float y1[SB_HRAD_H1], y2[SB_HRAD_H2];
   int r = 0, y = 0;
   const bool ok = hrad_source(a, &r, &y);
+  for (int i = threadIdx.x; i < SB_HRAD_H1; i += SB_HRAD_H2) y1[i] = a.y1[i];
   __syncthreads();
-  float acc = 0.0f;
-#pragma unroll
-  for (int i = 0; i < STEPS; ++i) {
-    const f32x4 v = *(const f32x4 *)&y1[(i * LPU + part) * 4];
-    acc += (wv[i][0] * v[0] + wv[i][1] * v[1]) + (wv[i][2] * v[2] + wv[i][3] * v[3]);
-  }
-#pragma unroll
-  for (int o = 1; o < LPU; o <<= 1) acc += __shfl_xor(acc, o, 64);
-  if (part == 0) y2[m] = fmaxf(acc + b2, 0.0f);
-  __syncthreads();
-  static_assert(SB_HRAD_H2 == 64 && SB_HRAD_CLASSES <= kTailThreads / 64, "a wave per class");
-  if (w < SB_HRAD_CLASSES) {
-    float v = w3 * y2[lane];
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (lane == 0) lg[w] = v + b3;
+  {
+    const int m = threadIdx.x;
+    const float *w = a.w2 + (size_t)m * SB_HRAD_H1;
+    float acc = 0.0f;
+    for (int i = 0; i < SB_HRAD_H1; ++i) acc += w[i] * y1[i];
+    y2[m] = fmaxf(acc + a.b2[m], 0.0f);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
+    float lg[SB_HRAD_CLASSES];
     int best = 0;
-    for (int c = 1; c < SB_HRAD_CLASSES; ++c)
-      if (lg[c] > lg[best]) best = c;
+    for (int c = 0; c < SB_HRAD_CLASSES; ++c) {
+      const float *w = a.w3 + (size_t)c * SB_HRAD_H2;
+      float acc = 0.0f;
+      for (int i = 0; i < SB_HRAD_H2; ++i) acc += w[i] * y2[i];
+      lg[c] = acc + a.b3[c];
+      if (c > 0 && lg[c] > lg[best]) best = c;
+    }
     for (int c = 0; c < SB_HRAD_CLASSES; ++c) a.logits3[c] = ok ? lg[c] : 0.0f;
     *a.cls = ok ? best : -1;
   }
@@ -140,7 +100,7 @@ __global__ __launch_bounds__(kTailThreads) void k_hrad_tail(HradArgs a) {
 hipError_t launch_hrad(const HradArgs &a, hipStream_t s) {
   if (a.hidden % 8 != 0 || a.k < 1) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_hrad_l1, dim3(SB_HRAD_H1), dim3(kL1Threads), 0, s, a);
-  hipLaunchKernelGGL(k_hrad_tail, dim3(1), dim3(kTailThreads), 0, s, a);
+  hipLaunchKernelGGL(k_hrad_tail, dim3(1), dim3(SB_HRAD_H2), 0, s, a);
   return hipGetLastError();
 }
 

@@ -816,24 +816,30 @@ size_t sb_sample_workspace_bytes(int32_t vocab) {
   return sample_ws_bytes(vocab);
 }
 
-sb_status sb_select_branch(int32_t vocab, const float *d_logits_row,
-                           const sb_row_stats *d_stats_row, float temperature, int32_t n_cand,
-                           const int32_t *d_cand_tokens, const float *d_q, const float *d_u,
-                           int32_t *d_out, void *d_ws, size_t ws_bytes, hipStream_t stream) {
+// sb_select_branch and sb_accept_resample with the walk's waits as arguments
+// (WalkWait), for the tests of what a workgroup that gives up leaves behind.
+sb_status sb_internal_select_branch(int32_t vocab, const float *d_logits_row,
+                                    const sb_row_stats *d_stats_row, float temperature,
+                                    int32_t n_cand, const int32_t *d_cand_tokens, const float *d_q,
+                                    const float *d_u, int32_t *d_out, void *d_ws, size_t ws_bytes,
+                                    hipStream_t stream, uint64_t ticks, int32_t lo, int32_t hi,
+                                    int32_t at) {
   if (vocab < 1 || !d_logits_row || !d_stats_row || !d_cand_tokens || !d_q || !d_u || !d_out ||
       !d_ws || !temperature_ok(temperature))
     return SB_ERR_INVALID_ARG;
   if (n_cand < 1 || n_cand > SB_MAX_ROWS) return SB_ERR_INVALID_ARG;
   if (ws_bytes < sample_ws_bytes(vocab)) return SB_ERR_CAPACITY;
   return hip_status(launch_select(vocab, d_logits_row, d_stats_row, temperature, n_cand,
-                                  d_cand_tokens, d_q, d_u, d_out, d_ws, stream));
+                                  d_cand_tokens, d_q, d_u, d_out, d_ws, stream,
+                                  WalkWait{ticks, lo, hi, at}));
 }
 
-sb_status sb_accept_resample(int32_t vocab, int32_t n_rows, const int32_t *d_tokens,
-                             const int32_t *h_parents, const float *d_logits,
-                             const sb_row_stats *d_stats, float temperature, const float *d_q,
-                             const float *d_u, sb_step_result *d_result, void *d_ws,
-                             size_t ws_bytes, hipStream_t stream) {
+sb_status sb_internal_accept_resample(int32_t vocab, int32_t n_rows, const int32_t *d_tokens,
+                                      const int32_t *h_parents, const float *d_logits,
+                                      const sb_row_stats *d_stats, float temperature,
+                                      const float *d_q, const float *d_u, sb_step_result *d_result,
+                                      void *d_ws, size_t ws_bytes, hipStream_t stream,
+                                      uint64_t ticks, int32_t lo, int32_t hi, int32_t at) {
   if (vocab < 1 || !d_tokens || !d_logits || !d_stats || !d_q || !d_u || !d_result || !d_ws ||
       !temperature_ok(temperature))
     return SB_ERR_INVALID_ARG;
@@ -842,7 +848,26 @@ sb_status sb_accept_resample(int32_t vocab, int32_t n_rows, const int32_t *d_tok
   if (st != SB_OK) return st;
   if (ws_bytes < sample_ws_bytes(vocab)) return SB_ERR_CAPACITY;
   return hip_status(launch_walk(vocab, tree, d_tokens, d_logits, d_stats, temperature, d_q, d_u,
-                                d_result, d_ws, stream));
+                                d_result, d_ws, stream, WalkWait{ticks, lo, hi, at}));
+}
+
+sb_status sb_select_branch(int32_t vocab, const float *d_logits_row,
+                           const sb_row_stats *d_stats_row, float temperature, int32_t n_cand,
+                           const int32_t *d_cand_tokens, const float *d_q, const float *d_u,
+                           int32_t *d_out, void *d_ws, size_t ws_bytes, hipStream_t stream) {
+  return sb_internal_select_branch(vocab, d_logits_row, d_stats_row, temperature, n_cand,
+                                   d_cand_tokens, d_q, d_u, d_out, d_ws, ws_bytes, stream,
+                                   kWalkWait.ticks, kWalkWait.lo, kWalkWait.hi, kWalkWait.at);
+}
+
+sb_status sb_accept_resample(int32_t vocab, int32_t n_rows, const int32_t *d_tokens,
+                             const int32_t *h_parents, const float *d_logits,
+                             const sb_row_stats *d_stats, float temperature, const float *d_q,
+                             const float *d_u, sb_step_result *d_result, void *d_ws,
+                             size_t ws_bytes, hipStream_t stream) {
+  return sb_internal_accept_resample(vocab, n_rows, d_tokens, h_parents, d_logits, d_stats,
+                                     temperature, d_q, d_u, d_result, d_ws, ws_bytes, stream,
+                                     kWalkWait.ticks, kWalkWait.lo, kWalkWait.hi, kWalkWait.at);
 }
 
 sb_status sb_model_set_forward(sb_model *m, int32_t mode) {

@@ -21,7 +21,10 @@
 // decisions from the same values; after a rejection each publishes its
 // slice's mass and the residual at the next candidate's token, and reads
 // everyone else's.  A draw looks up the slice masses it already has; only the
-// workgroup of the crossing slice searches its tokens.  Measured (the walk
+// workgroup of the crossing slice searches its tokens, and sends the one it
+// finds to workgroup 0, which alone writes the result: when any message it
+// needs stays out (a workgroup that gave up, or that the chip has no room for)
+// it does the walk again by itself with p~ in memory.  Measured (the walk
 // with a rejection or two, one workgroup of 1024 threads -> these): 37 rows at
 // 128256 tokens 61 -> 11 us, 33 rows at 32000 tokens 23 -> 12 us, and 1.4 us
 // for the launch that clears the messages.
@@ -39,10 +42,6 @@ namespace {
 constexpr int kT = 256;  // threads of a workgroup
 constexpr int kNW = kT / 64;
 constexpr int kMaxG = 256;  // workgroups: one thread per slice mass
-// Ticks of the 100 MHz s_memrealtime counter a workgroup waits for the others
-// (50 ms; they arrive within microseconds unless the chip cannot hold them).
-constexpr unsigned long long kWaitTicks = 5000000ull;
-
 __device__ __forceinline__ double wave_sum(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
@@ -81,14 +80,17 @@ struct WalkShared {
   double part[kNW], part2[kNW];
   double z, cap;
   int fail, first, last;
+  int32_t token;  // the draw's
 };
 
-// Messages between the workgroups: per exchange and workgroup two words, the
+// Messages between the workgroups.  Word 0 is the drawn token + 1 (0: not there
+// yet), sent to workgroup 0.  Then per exchange and workgroup two words, the
 // complement of a float64's bits (a NaN as the canonical one), never 0; 0 is
 // "not there yet".  Three sets take turns: exchange k uses set k % 3, and its
 // publisher first clears its words of set (k + 1) % 3 -- they held exchange
 // k - 2, which everyone has read, since everyone published k - 1 after it --
-// and waits for that store, so who sees message k sees the cleared words.
+// and waits for that store, so who sees message k sees the cleared words.  Only
+// word 0 and the first set are clear before the launch.
 // Words move with device-scope relaxed stores and loads; the message is the
 // data, nothing else crosses workgroups.
 __device__ __forceinline__ unsigned long long encode(double v) {
@@ -158,13 +160,14 @@ __device__ int block_cross(double mass, double inc, double thr, WalkShared &sh) 
 template <int EPT>
 struct Slices {
   int vocab, vec4, G, g, v0;
-  unsigned long long *msg;  // [3][G][2]
+  unsigned long long *msg;  // 1 + [3][G][2]
   int k;                    // exchanges so far
+  WalkWait wait;
   double x[EPT], scale, zdiv;
   double mass;  // of workgroup threadIdx.x's slice, once have_mass
   bool have_mass;
 
-  __device__ void init(int vocab_, int vec4_, unsigned long long *msg_) {
+  __device__ void init(int vocab_, int vec4_, const WalkWait &wait_, unsigned long long *msg_) {
     vocab = vocab_;
     vec4 = vec4_;
     G = gridDim.x;
@@ -172,7 +175,10 @@ struct Slices {
     v0 = (g * kT + (int)threadIdx.x) * EPT;
     msg = msg_;
     k = 0;
+    wait = wait_;
   }
+  // This workgroup does not wait now (a test's).
+  __device__ __forceinline__ bool gives_up() const { return g >= wait.lo && g < wait.hi && k >= wait.at; }
   __device__ __forceinline__ void load(const float *row, float (&f)[EPT]) const {
     const __amdgpu_buffer_rsrc_t rs = uniform_rsrc(row, vocab * 4);
     if (vec4) {
@@ -207,8 +213,9 @@ struct Slices {
     if (threadIdx.x == 0) sh.fail = 0;
     double s = threadIdx.x == 0 ? sum : 0.0, c = threadIdx.x == 0 ? cap : 0.0;
     if (G > 1) {
-      unsigned long long *cur = msg + (size_t)(k % 3) * G * 2;
-      unsigned long long *nxt = msg + (size_t)((k + 1) % 3) * G * 2;
+      unsigned long long *cur = msg + 1 + (size_t)(k % 3) * G * 2;
+      unsigned long long *nxt = msg + 1 + (size_t)((k + 1) % 3) * G * 2;
+      const bool leave = gives_up();
       ++k;
       if (threadIdx.x == 0) {
         put(nxt + 2 * g, 0ull);
@@ -225,8 +232,8 @@ struct Slices {
         for (;;) {
           if (!x) x = get(cur + 2 * threadIdx.x);
           if (!y) y = get(cur + 2 * threadIdx.x + 1);
-          if (x && y) break;
-          if (__builtin_amdgcn_s_memrealtime() - t0 > kWaitTicks) {
+          if (x && y && !leave) break;
+          if (leave || __builtin_amdgcn_s_memrealtime() - t0 > wait.ticks) {
             sh.fail = 1;
             break;
           }
@@ -276,7 +283,8 @@ struct Slices {
     for (int e = 0; e < EPT; ++e) cap = v0 + e == v ? x[e] : cap;
     return exchange(0.0, cap, own, sh);
   }
-  __device__ bool draw(float u, int32_t *out, WalkShared &sh) {
+  // In workgroup 0 sh.token is the token; false there when it stays out.
+  __device__ bool draw(float u, WalkShared &sh) {
     double ts = 0.0;
 #pragma unroll
     for (int e = 0; e < EPT; ++e) ts += x[e];
@@ -287,28 +295,48 @@ struct Slices {
     const double thr = (double)u * sh.z;
     const int cross = block_cross(m, inc, thr, sh);
     if (cross < 0) {
-      if (g == 0 && threadIdx.x == 0) *out = vocab - 1;
+      if (threadIdx.x == 0) sh.token = vocab - 1;
       return true;
     }
-    if (cross != g) return true;
-    if ((int)threadIdx.x == cross) sh.cap = inc - m;
-    __syncthreads();
-    const double base = sh.cap, tinc = base + block_scan(ts, sh);
-    const int at = block_cross(ts, tinc, thr, sh);
-    if ((int)threadIdx.x == (at < 0 ? 0 : at)) {
-      int found = -1, last = v0;
-      double c = tinc - ts;
+    if (cross == g) {
+      if ((int)threadIdx.x == cross) sh.cap = inc - m;
+      __syncthreads();
+      const double base = sh.cap, tinc = base + block_scan(ts, sh);
+      const int at = block_cross(ts, tinc, thr, sh);
+      if ((int)threadIdx.x == (at < 0 ? 0 : at)) {
+        int found = -1, last = v0;
+        double c = tinc - ts;
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        c += x[e];
-        if (x[e] > 0.0) {
-          last = v0 + e;
-          if (found < 0 && c > thr) found = v0 + e;
+        for (int e = 0; e < EPT; ++e) {
+          c += x[e];
+          if (x[e] > 0.0) {
+            last = v0 + e;
+            if (found < 0 && c > thr) found = v0 + e;
+          }
+        }
+        sh.token = found >= 0 ? found : last;
+        if (g != 0) put(msg, (unsigned long long)sh.token + 1);
+      }
+      return true;
+    }
+    if (g != 0) return true;
+    if (threadIdx.x == 0) {
+      const bool leave = gives_up();
+      const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+      unsigned long long w;
+      sh.fail = 0;
+      for (;;) {
+        w = get(msg);
+        if (w && !leave) break;
+        if (leave || __builtin_amdgcn_s_memrealtime() - t0 > wait.ticks) {
+          sh.fail = 1;
+          break;
         }
       }
-      *out = found >= 0 ? found : last;
+      sh.token = (int32_t)w - 1;
     }
-    return true;
+    __syncthreads();
+    return sh.fail == 0;
   }
 };
 
@@ -362,7 +390,7 @@ struct InMemory {
     __syncthreads();
     return true;
   }
-  __device__ bool draw(float u, int32_t *out, WalkShared &sh) {
+  __device__ bool draw(float u, WalkShared &sh) {
     const int seg = (vocab + kT - 1) / kT, lo = threadIdx.x * seg, hi = min(vocab, lo + seg);
     double ts = 0.0;
     for (int v = lo; v < hi; ++v) ts += cur(v);
@@ -372,7 +400,7 @@ struct InMemory {
     const double thr = (double)u * sh.z;
     const int at = block_cross(ts, inc, thr, sh);
     if (at < 0) {
-      if (threadIdx.x == 0) *out = vocab - 1;
+      if (threadIdx.x == 0) sh.token = vocab - 1;
     } else if ((int)threadIdx.x == at) {
       int found = -1, last = lo;
       double c = inc - ts;
@@ -384,7 +412,7 @@ struct InMemory {
           if (found < 0 && c > thr) found = v;
         }
       }
-      *out = found >= 0 ? found : last;
+      sh.token = found >= 0 ? found : last;
     }
     return true;
   }
@@ -434,12 +462,12 @@ __device__ __forceinline__ bool accept(const WalkIn &a, const WalkRows &R, int c
   return (double)R.u[c] < ratio;
 }
 
-// The walk from the root.  Returns false when the distribution's owner gave up; else *out_tok has the final
-// token if this workgroup is the one to write it (`select`: only without an
-// acceptance).  *kept: the last accepted row (0: none), bonus: a leaf.
+// The walk from the root.  Returns false when a message stayed out; else sh.token
+// is workgroup 0's drawn token (`select`: only without an acceptance), *bonus
+// whether a leaf was reached.
 template <class D>
-__device__ bool walk_run(D &d, const WalkIn &a, WalkRows &R, WalkShared &sh, bool select,
-                         int32_t *out_tok, int *nrej, int *bonus) {
+__device__ bool walk_run(D &d, const WalkIn &a, WalkRows &R, WalkShared &sh, bool select, int *nrej,
+                         int *bonus) {
   for (;;) {
     // While a node's first candidate is accepted against the node's own row,
     // the tests read LDS only, and one thread walks them.  The failing one is
@@ -474,7 +502,7 @@ __device__ bool walk_run(D &d, const WalkIn &a, WalkRows &R, WalkShared &sh, boo
     d.set_row(row_of(a, R.st[node]), a.logits + (size_t)node * a.vocab);
     if (nk == 0) {
       *bonus = 1;
-      return d.draw(a.u[a.u_draw], out_tok, sh);
+      return d.draw(a.u[a.u_draw], sh);
     }
     int acc = -1;
     bool resid = false;  // p~ is a residual
@@ -507,7 +535,7 @@ __device__ bool walk_run(D &d, const WalkIn &a, WalkRows &R, WalkShared &sh, boo
       }
       __syncthreads();
     }
-    if (acc < 0) return d.draw(a.u[a.u_draw], out_tok, sh);
+    if (acc < 0) return d.draw(a.u[a.u_draw], sh);
     if (threadIdx.x == 0) {
       R.path[R.plen++] = (int16_t)acc;
       R.node = acc;
@@ -554,36 +582,35 @@ __device__ void walk_rows(const WalkIn &a, const TreeArg *tree, WalkRows &R) {
 
 // EPT tokens per thread (0: one workgroup, p~ in memory).
 template <int EPT, bool SELECT>
-__global__ __launch_bounds__(kT) void k_walk(WalkIn a, TreeArg tree, int vec4,
+__global__ __launch_bounds__(kT) void k_walk(WalkIn a, TreeArg tree, int vec4, WalkWait wait,
                                              sb_step_result *__restrict__ result,
                                              int32_t *__restrict__ out,
                                              unsigned long long *msg, double *arr) {
   __shared__ WalkRows R;
   __shared__ WalkShared sh;
   walk_rows(a, SELECT ? nullptr : &tree, R);
-  int32_t *tok = SELECT ? out + 1 : &result->next_token;
   int nrej = 0, bonus = 0;
   bool done = false;
   if constexpr (EPT > 0) {
     Slices<EPT> d;
-    d.init(a.vocab, vec4, msg);
-    done = walk_run(d, a, R, sh, SELECT, tok, &nrej, &bonus);
+    d.init(a.vocab, vec4, wait, msg);
+    done = walk_run(d, a, R, sh, SELECT, &nrej, &bonus);
   }
-  if (blockIdx.x != 0) return;
+  if (blockIdx.x != 0) return;  // the result is workgroup 0's alone
   if (!done) {
     if (EPT > 0) walk_rows(a, SELECT ? nullptr : &tree, R);
     nrej = bonus = 0;
     InMemory d;
     d.vocab = a.vocab;
     d.arr = arr;
-    walk_run(d, a, R, sh, SELECT, tok, &nrej, &bonus);
+    walk_run(d, a, R, sh, SELECT, &nrej, &bonus);
   }
   __syncthreads();
   if constexpr (SELECT) {
     if (threadIdx.x == 0) {
       const int acc = R.plen > 1 ? R.path[1] - 1 : -1;
       out[0] = acc;
-      if (acc >= 0) out[1] = R.tok[acc + 1];
+      out[1] = acc >= 0 ? R.tok[acc + 1] : sh.token;
       out[2] = R.flags;
     }
   } else {
@@ -596,6 +623,7 @@ __global__ __launch_bounds__(kT) void k_walk(WalkIn a, TreeArg tree, int vec4,
       }
       result->n_accepted = R.plen - 1;
       result->branch = branch;
+      result->next_token = sh.token;
       result->path_len = R.plen;
       result->flags = R.flags;
       result->n_rejected = nrej;
@@ -615,7 +643,7 @@ __global__ __launch_bounds__(kT) void k_walk_clear(unsigned long long *p, int n)
 // 256 workgroups of 8192 one workgroup with p~ in memory.
 template <bool SELECT>
 hipError_t launch(const WalkIn &a, const TreeArg &tree, sb_step_result *result, int32_t *out,
-                  void *ws, hipStream_t s) {
+                  void *ws, hipStream_t s, const WalkWait &wait) {
   double *arr = (double *)ws;  // 2 vocab float64: the residual, then the messages
   unsigned long long *msg = (unsigned long long *)(arr + a.vocab);
   const int vec4 = (a.vocab & 3) == 0;
@@ -623,26 +651,26 @@ hipError_t launch(const WalkIn &a, const TreeArg &tree, sb_step_result *result, 
   while (ept < 32 && (a.vocab + kT * ept - 1) / (kT * ept) > 64) ept *= 2;
   const int G = (a.vocab - 1) / (kT * ept) + 1;
   if (G > kMaxG) {
-    hipLaunchKernelGGL((k_walk<0, SELECT>), dim3(1), dim3(kT), 0, s, a, tree, vec4, result, out, msg, arr);
+    hipLaunchKernelGGL((k_walk<0, SELECT>), dim3(1), dim3(kT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
     return hipGetLastError();
   }
   if (G > 1) {
-    hipLaunchKernelGGL(k_walk_clear, dim3(1), dim3(kT), 0, s, msg, 3 * G * 2);
+    hipLaunchKernelGGL(k_walk_clear, dim3(1), dim3(kT), 0, s, msg, 1 + 2 * G);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   switch (ept) {
     case 4:
-      hipLaunchKernelGGL((k_walk<4, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, result, out, msg, arr);
+      hipLaunchKernelGGL((k_walk<4, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
       break;
     case 8:
-      hipLaunchKernelGGL((k_walk<8, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, result, out, msg, arr);
+      hipLaunchKernelGGL((k_walk<8, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
       break;
     case 16:
-      hipLaunchKernelGGL((k_walk<16, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, result, out, msg, arr);
+      hipLaunchKernelGGL((k_walk<16, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
       break;
     default:
-      hipLaunchKernelGGL((k_walk<32, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, result, out, msg, arr);
+      hipLaunchKernelGGL((k_walk<32, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
   }
   return hipGetLastError();
 }
@@ -668,19 +696,21 @@ size_t sample_ws_bytes(int vocab) { return (size_t)2 * (size_t)vocab * sizeof(do
 
 hipError_t launch_walk(int vocab, const TreeArg &tree, const int32_t *tokens, const float *logits,
                        const sb_row_stats *stats, float temperature, const float *q,
-                       const float *u, sb_step_result *result, void *ws, hipStream_t s) {
+                       const float *u, sb_step_result *result, void *ws, hipStream_t s,
+                       const WalkWait &wait) {
   return launch<false>(walk_in(vocab, tree.n, temperature, tokens, logits, stats, q, u), tree,
-                       result, nullptr, ws, s);
+                       result, nullptr, ws, s, wait);
 }
 
 hipError_t launch_select(int vocab, const float *logits_row, const sb_row_stats *stats_row,
                          float temperature, int n_cand, const int32_t *cand_tokens,
-                         const float *q, const float *u, int32_t *out, void *ws, hipStream_t s) {
+                         const float *q, const float *u, int32_t *out, void *ws, hipStream_t s,
+                         const WalkWait &wait) {
   WalkIn a = walk_in(vocab, n_cand + 1, temperature, cand_tokens, logits_row, stats_row, q, u);
   a.off = 1;
   a.u_draw = n_cand;
   const TreeArg none{};
-  return launch<true>(a, none, nullptr, out, ws, s);
+  return launch<true>(a, none, nullptr, out, ws, s, wait);
 }
 
 }  // namespace sb

@@ -34,12 +34,23 @@ struct LmPart {
 // groups' partials, part[row][groups] (at most 256 groups).
 hipError_t launch_stats_finish(const LmPart *part, int groups, int n_rows, float temperature,
                                sb_row_stats *stats, hipStream_t s);
+// How long a workgroup of the walk waits for the others' messages: ticks of the
+// 100 MHz s_memrealtime counter (50 ms; they arrive within microseconds unless
+// the chip cannot hold them all).  Workgroups lo .. hi - 1 do not wait at all
+// from exchange `at` on (for tests; none otherwise).
+struct WalkWait {
+  unsigned long long ticks;
+  int lo, hi, at;
+};
+constexpr WalkWait kWalkWait{5000000ull, 0, 0, 0};
 hipError_t launch_walk(int vocab, const TreeArg &tree, const int32_t *tokens, const float *logits,
                        const sb_row_stats *stats, float temperature, const float *q,
-                       const float *u, sb_step_result *result, void *ws, hipStream_t s);
+                       const float *u, sb_step_result *result, void *ws, hipStream_t s,
+                       const WalkWait &wait = kWalkWait);
 hipError_t launch_select(int vocab, const float *logits_row, const sb_row_stats *stats_row,
                          float temperature, int n_cand, const int32_t *cand_tokens,
-                         const float *q, const float *u, int32_t *out, void *ws, hipStream_t s);
+                         const float *q, const float *u, int32_t *out, void *ws, hipStream_t s,
+                         const WalkWait &wait = kWalkWait);
 size_t sample_ws_bytes(int vocab);
 // Rows of a draft sample call: logits/stats row src[i] -> token and q row dst[i].
 struct DraftRows {

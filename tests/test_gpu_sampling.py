@@ -6,6 +6,7 @@ given the same uniforms, except where the oracle's own path passes within
 1e-6 of a threshold (|u - p~/q| or |u*W - C_v| / W), where summation order
 and exp ulps may legitimately flip a decision.
 """
+import ctypes as C
 import json
 import os
 
@@ -243,6 +244,87 @@ def test_select_slices(api, vocab, T):
         assert got == want, (seed, got, want)
         checked += 1
     assert checked >= 1
+
+
+def _slice_tokens(vocab):
+    """Tokens of one workgroup's slice of the vocabulary (k_walk.hip)."""
+    per = 1024
+    while per < 8192 and -(-vocab // per) > 64:
+        per *= 2
+    return per
+
+
+def _all_rejected(vocab, n, T, seed):
+    """A target row and n candidates that are far likelier under their own
+    rows than under it, tested with u = 0.9: every one is rejected.  The last
+    token is a likely one (it may be a slice of its own)."""
+    lg = synth.random_logits(1, vocab, 2.0, seed=seed)[0]
+    lg[-1] = lg.max()
+    p = sampling.target_probs(lg, T)
+    q = synth.softmax_rows(synth.random_logits(n, vocab, 2.0, seed=seed + 1)).astype(np.float32)
+    toks = np.argmax(q - 20.0 * p, axis=1).astype(np.int32)
+    return lg, p, q, toks, np.full(n, 0.9, np.float32)
+
+
+def _uniform_into(pt, lo, hi):
+    """The uniform whose draw from the weights pt is the heaviest of tokens
+    lo .. hi - 1, in the middle of its range."""
+    c = np.cumsum(pt)
+    y = lo + int(np.argmax(pt[lo:hi]))
+    return np.float32((c[y] - 0.5 * pt[y]) / c[-1])
+
+
+@pytest.mark.parametrize("vocab", [2049, 5000, 70001])
+@pytest.mark.parametrize("walk", [False, True])
+def test_walk_gives_up(api, vocab, walk):
+    """Workgroups that do not wait for a message (forced from the host; every
+    kernel ends normally) leave a whole and right result, whichever they are:
+    workgroup 0, the one whose slice the draw crosses, every other, all; from
+    each exchange on.  The result holds a sentinel before every call."""
+    name = "sb_internal_" + ("accept_resample" if walk else "select_branch")
+    f = getattr(api.lib, name)
+    f.restype = C.c_int32
+    f.argtypes = (api.lib.sb_accept_resample if walk else api.lib.sb_select_branch).argtypes + [C.c_uint64] + [C.c_int32] * 3
+    per = _slice_tokens(vocab)
+    G = -(-vocab // per)
+    n = 3
+    lg, p, q, toks, u = _all_rejected(vocab, n, 1.0, vocab)
+    pt = sampling.branch_select(p, toks, q, u).p_tilde
+    st = api.new_stats(n + 1)
+    rows = np.stack([lg] * (n + 1))
+    dl = dev(rows)
+    api.sb_softmax_stats(dl, 1.0, st)
+    ws = torch.full((api.sb_sample_workspace_bytes(vocab),), 0x5a, dtype=torch.uint8, device="cuda")
+    dt = dev(np.concatenate([[0], toks]).astype(np.int32))
+    dq = dev(np.concatenate([q[:1], q]))
+    par = np.array([-1] + [0] * n, np.int32)
+    for owner in sorted({0, G // 2, G - 1}):
+        uf = _uniform_into(pt, owner * per, min(vocab, (owner + 1) * per))
+        tr = []
+        ref = sampling.accept_resample(np.concatenate([[0], toks]), par, rows, 1.0, np.concatenate([q[:1], q]),
+                                       np.concatenate([[uf], u]), trace=tr)
+        assert ref.n_rejected == n and ref.next_token // per == owner
+        assert decision_margin(tr, np.concatenate([[uf], u])) > TIE
+        du = dev(np.concatenate([[uf], u]) if walk else np.concatenate([u, [uf]]))
+        for lo, hi in [(0, 0), (0, 1), (owner, owner + 1), (1, G), (0, G)]:
+            for at in range(n + 1):
+                say(f"{name} vocab={vocab} owner={owner} gives up {lo}..{hi} from {at}")
+                out = torch.full((264,), -7, dtype=torch.int32, device="cuda")
+                tail = (du.data_ptr(), out.data_ptr(), ws.data_ptr(), ws.numel(), api._stream(), 100000, lo, hi, at)
+                if walk:
+                    rc = f(vocab, n + 1, dt.data_ptr(), par.ctypes.data_as(C.POINTER(C.c_int32)), dl.data_ptr(),
+                           st.data_ptr(), 1.0, dq.data_ptr(), *tail)
+                else:
+                    rc = f(vocab, dl.data_ptr(), st.data_ptr(), 1.0, n, dt[1:].data_ptr(), dq[1:].data_ptr(), *tail)
+                assert rc == 0
+                o = out.cpu().numpy()
+                if walk:
+                    got = api.decode_result(out)
+                    assert got["next_token"] == ref.next_token, (lo, hi, at)
+                    assert got["path"] == [0] and got["n_accepted"] == 0 and got["branch"] == -1
+                    assert (got["flags"], got["n_rejected"], got["bonus"]) == (0, n, 0)
+                else:
+                    assert o[:3].tolist() == [-1, ref.next_token, 0], (lo, hi, at)
 
 
 def test_walk_flags(api):

@@ -444,8 +444,10 @@ struct WalkIn {
   int u_draw;          // index of the final draw's uniform
 };
 
+// A row whose total is not finite (a NaN or +inf logit, an invalid forward) has
+// no mass at T > 0: its every raw(v) is NaN.
 __device__ __forceinline__ Row row_of(const WalkIn &a, const sb_row_stats &s) {
-  return Row{a.inv_t, s.zmax, s.total, s.argmax, a.greedy};
+  return Row{a.inv_t, isfinite(s.total) ? s.zmax : NAN, s.total, s.argmax, a.greedy};
 }
 
 // The accept test of row c against p~(its token) = px (thread 0).

@@ -327,6 +327,55 @@ def test_walk_gives_up(api, vocab, walk):
                     assert o[:3].tolist() == [-1, ref.next_token, 0], (lo, hi, at)
 
 
+@pytest.mark.parametrize("vocab", [64, 5000, 70001])
+@pytest.mark.parametrize("bad", ["nan first", "nan last", "inf", "marked"])
+@pytest.mark.parametrize("T", [1.0, 0.0])
+def test_walk_nonfinite_row(api, vocab, bad, T):
+    """A row that is not finite has no mass at T > 0: the draw from it is the
+    last token, wherever the NaN or infinity stands, and also where only its
+    total says so (a forward that was not valid); at T = 0 it is its argmax.
+    By the workgroups together and by workgroup 0 alone, with no candidate
+    (the bonus draw) and after two rejections."""
+    lg, p, q, toks, u = _all_rejected(vocab, 2, 1.0, 40 + vocab)
+    lg[-1] = lg.min()  # not the argmax
+    if bad.startswith("nan"):
+        lg[3 if bad == "nan first" else vocab - 2] = np.nan
+    elif bad == "inf":
+        lg[vocab // 2] = np.inf
+    ref_st = sampling.row_stats(lg, T)
+    st = api.new_stats(3)
+    rows = np.stack([lg] * 3)
+    dl = dev(rows)
+    api.sb_softmax_stats(dl, T, st)
+    if bad == "marked":
+        ref_st.total = float("nan")
+        st.view(torch.float64)[:, 1] = float("nan")
+    stats = [ref_st] * 3
+    ws = torch.empty(api.sb_sample_workspace_bytes(vocab), dtype=torch.uint8, device="cuda")
+    f = api.lib.sb_internal_accept_resample
+    f.restype = C.c_int32
+    f.argtypes = api.lib.sb_accept_resample.argtypes + [C.c_uint64] + [C.c_int32] * 3
+    tok3, q3 = np.concatenate([[0], toks]).astype(np.int32), np.concatenate([q[:1], q])
+    u3 = np.concatenate([[0.4], u]).astype(np.float32)
+    dt, dq, du = dev(tok3), dev(q3), dev(u3)
+    for n in (1, 3):
+        par = np.array([-1, 0, 0][:n], np.int32)
+        with np.errstate(invalid="ignore"):
+            ref = sampling.accept_resample(tok3, par, rows, T, q3, u3, stats=stats)
+        if T > 0:
+            assert ref.next_token == vocab - 1
+        for hi in (0, 1):
+            say(f"non-finite row vocab={vocab} {bad} T={T} n={n} gives up 0..{hi}")
+            out = api.new_result()
+            assert f(vocab, n, dt.data_ptr(), par.ctypes.data_as(C.POINTER(C.c_int32)), dl.data_ptr(), st.data_ptr(), T,
+                     dq.data_ptr(), du.data_ptr(), out.data_ptr(), ws.data_ptr(), ws.numel(), api._stream(), 100000, 0, hi,
+                     0) == 0
+            got = api.decode_result(out)
+            assert got["next_token"] == ref.next_token
+            assert got["flags"] == ref.flags and got["flags"] & api.SB_FLAG_NONFINITE
+            assert (got["n_rejected"], bool(got["bonus"])) == (ref.n_rejected, ref.bonus)
+
+
 def test_walk_flags(api):
     vocab = 64
     parents = synth.branch_parents(2, 2)

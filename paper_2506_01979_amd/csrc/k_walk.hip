@@ -39,8 +39,8 @@
 namespace sb {
 namespace {
 
-constexpr int kT = 256;  // threads of a workgroup
-constexpr int kNW = kT / 64;
+constexpr int kT = 256;      // threads of a workgroup
+constexpr int kMemT = 1024;  // of the one past the slices' reach
 constexpr int kMaxG = 256;  // workgroups: one thread per slice mass
 __device__ __forceinline__ double wave_sum(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -77,7 +77,7 @@ struct Row {
 };
 
 struct WalkShared {
-  double part[kNW], part2[kNW];
+  double part[kMemT / 64], part2[kMemT / 64];
   double z, cap;
   int fail, first, last;
   int32_t token;  // the draw's
@@ -108,6 +108,7 @@ __device__ __forceinline__ unsigned long long get(const unsigned long long *p) {
 }
 
 // Block-wide sums of v and c (every thread gets them).
+template <int NT>
 __device__ void block_sum2(double &v, double &c, WalkShared &sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   v = wave_sum(v);
@@ -117,8 +118,12 @@ __device__ void block_sum2(double &v, double &c, WalkShared &sh) {
     sh.part2[w] = c;
   }
   __syncthreads();
-  v = (sh.part[0] + sh.part[1]) + (sh.part[2] + sh.part[3]);
-  c = (sh.part2[0] + sh.part2[1]) + (sh.part2[2] + sh.part2[3]);
+  v = c = 0.0;
+#pragma unroll
+  for (int k = 0; k < NT / 64; k += 4) {
+    v += (sh.part[k] + sh.part[k + 1]) + (sh.part[k + 2] + sh.part[k + 3]);
+    c += (sh.part2[k] + sh.part2[k + 1]) + (sh.part2[k + 2] + sh.part2[k + 3]);
+  }
   __syncthreads();
 }
 
@@ -159,6 +164,7 @@ __device__ int block_cross(double mass, double inc, double thr, WalkShared &sh) 
 // registers, thread t the EPT consecutive ones from v0.
 template <int EPT>
 struct Slices {
+  static constexpr int kThreads = kT;
   int vocab, vec4, G, g, v0;
   unsigned long long *msg;  // 1 + [3][G][2]
   int k;                    // exchanges so far
@@ -209,7 +215,7 @@ struct Slices {
   // cap) and reads everyone's: sh.z = the sum of the sums, sh.cap = the cap,
   // own = workgroup threadIdx.x's sum.  False when a message stays out.
   __device__ bool exchange(double sum, double cap, double &own, WalkShared &sh) {
-    block_sum2(sum, cap, sh);
+    block_sum2<kT>(sum, cap, sh);
     if (threadIdx.x == 0) sh.fail = 0;
     double s = threadIdx.x == 0 ? sum : 0.0, c = threadIdx.x == 0 ? cap : 0.0;
     if (G > 1) {
@@ -243,7 +249,7 @@ struct Slices {
       }
     }
     own = s;
-    block_sum2(s, c, sh);
+    block_sum2<kT>(s, c, sh);
     if (threadIdx.x == 0) {
       sh.z = s;
       sh.cap = c;
@@ -340,80 +346,162 @@ struct Slices {
   }
 };
 
-// The same by one workgroup with p~ in memory: after a message stayed out, and
-// for vocabularies past the slices' reach.
+// The same by one workgroup of NT threads with p~ in memory: after a message
+// stayed out, and for vocabularies past the slices' reach.  Bound by one compute
+// unit's path to memory, so every pass reads along the vocabulary, kBatch loads
+// of a thread in flight.  Three rejections and a draw at 2100001 tokens: 2.1 ms
+// (24 with a stretch of the vocabulary per thread); 256 threads after a give-up:
+// 79 us at 32000 tokens (205), 257 at 128256 (775).
+template <int NT>
 struct InMemory {
-  int vocab;
+  static constexpr int kThreads = NT, kBatch = 16;
+  // arr holds a residual r where r > 0 and elsewhere minus the p~ it was taken
+  // from, so a residual without mass, minus p~ everywhere, still has p~.
+  enum { kRow, kResidual, kKept };
+  int vocab, state;
   double *arr;
   Row row;
   const float *l;
   double scale, zdiv;
-  bool resid;
-  __device__ __forceinline__ double cur(int v) const { return resid ? arr[v] : row.raw(l[v], v); }
-  __device__ void set_row(const Row &r, const float *lrow) {
+  __device__ __forceinline__ void set_row(const Row &r, const float *lrow) {
     row = r;
     l = lrow;
     scale = r.scale();
-    resid = false;
+    state = kRow;
   }
-  __device__ bool reject(const float *q, int xcap, WalkShared &sh) {
-    // the residual is written over its input: keep the input when Z = 0 by
-    // summing first
-    double part = 0.0;
-    for (int v = threadIdx.x; v < vocab; v += kT) {
-      const double r = cur(v) * scale - (double)q[v];
-      part += r > 0.0 ? r : 0.0;
+  // p~ / scale at the tokens v (outside [0, hi): 0).
+  template <int K>
+  __device__ __forceinline__ void load(const int (&v)[K], int hi, double (&x)[K]) const {
+    if (state == kRow) {
+      const __amdgpu_buffer_rsrc_t rs = uniform_rsrc(l, vocab * 4);
+      float f[K];
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        f[k] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(rs, (v[k] < hi ? v[k] : vocab) * 4, 0, 0));
+#pragma unroll
+      for (int k = 0; k < K; ++k) x[k] = v[k] < hi ? row.raw(f[k], v[k]) : 0.0;
+    } else {
+      const __amdgpu_buffer_rsrc_t rs = uniform_rsrc(arr, vocab * 8);
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        x[k] = __builtin_bit_cast(
+            double, __builtin_amdgcn_raw_buffer_load_b64(rs, (v[k] < hi ? v[k] : vocab) * 8, 0, 0));
+#pragma unroll
+      for (int k = 0; k < K; ++k) x[k] = state == kKept ? -x[k] : x[k] > 0.0 ? x[k] : 0.0;
     }
-    double none = 0.0;
-    block_sum2(part, none, sh);
-    if (threadIdx.x == 0) {
-      sh.z = part;
-      sh.cap = 0.0;
-    }
+  }
+  __device__ __forceinline__ void load_run(int v0, int hi, double (&x)[kBatch]) const {
+    int v[kBatch];
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) v[b] = v0 + b;
+    load(v, hi, x);
+  }
+  __device__ __forceinline__ bool reject(const float *q, int xcap, WalkShared &sh) {
+    if (threadIdx.x == 0) sh.cap = 0.0;
     __syncthreads();
-    if (part > 0.0) {
-      for (int v = threadIdx.x; v < vocab; v += kT) {
-        double r = cur(v) * scale - (double)q[v];
-        r = r > 0.0 ? r : 0.0;
-        arr[v] = r;
-        if (v == xcap) sh.cap = r;
+    const __amdgpu_buffer_rsrc_t qrs = uniform_rsrc(q, vocab * 4);
+    double part = 0.0, none = 0.0;
+    for (int v0 = threadIdx.x; v0 < vocab; v0 += kBatch * NT) {
+      int v[kBatch];
+      float qv[kBatch];
+      double x[kBatch];
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) {
+        v[b] = v0 + b * NT;
+        qv[b] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(qrs, (v[b] < vocab ? v[b] : vocab) * 4, 0, 0));
       }
+      load(v, vocab, x);
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) {
+        const double r = x[b] * scale - (double)qv[b];
+        if (v[b] < vocab) {
+          arr[v[b]] = r > 0.0 ? r : -x[b];
+          part += r > 0.0 ? r : 0.0;
+          if (v[b] == xcap) sh.cap = r > 0.0 ? r : 0.0;
+        }
+      }
+    }
+    block_sum2<NT>(part, none, sh);
+    if (threadIdx.x == 0) sh.z = part;
+    if (part > 0.0) {
       zdiv = part;
       scale = 1.0 / zdiv;
-      resid = true;
+      state = kResidual;
+    } else if (state != kRow) {
+      state = kKept;
     }
     __syncthreads();
     return true;
   }
-  __device__ bool fetch(int v, WalkShared &sh) {
-    if (threadIdx.x == 0) sh.cap = cur(v);
+  __device__ __forceinline__ bool fetch(int v, WalkShared &sh) {
+    const int at[1] = {v};
+    double x[1];
+    load(at, vocab, x);
+    if (threadIdx.x == 0) sh.cap = x[0];
     __syncthreads();
     return true;
   }
-  __device__ bool draw(float u, WalkShared &sh) {
-    const int seg = (vocab + kT - 1) / kT, lo = threadIdx.x * seg, hi = min(vocab, lo + seg);
-    double ts = 0.0;
-    for (int v = lo; v < hi; ++v) ts += cur(v);
-    const double inc = block_scan(ts, sh);
-    if ((int)threadIdx.x == kT - 1) sh.z = inc;
+  // The wave whose stretch of the vocabulary crosses, then the thread whose run
+  // of that stretch does, then the token.
+  __device__ __forceinline__ bool draw(float u, WalkShared &sh) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int per = (vocab + NT / 64 - 1) / (NT / 64);
+    double mass = 0.0;
+    for (int v0 = w * per + lane; v0 < min(vocab, (w + 1) * per); v0 += kBatch * 64) {
+      int v[kBatch];
+      double x[kBatch];
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) v[b] = v0 + b * 64;
+      load(v, min(vocab, (w + 1) * per), x);
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) mass += x[b];
+    }
+    mass = wave_sum(mass);
+    if (lane != 0) mass = 0.0;
+    const double inc = block_scan(mass, sh);
+    if ((int)threadIdx.x == NT - 1) sh.z = inc;
     __syncthreads();
     const double thr = (double)u * sh.z;
-    const int at = block_cross(ts, inc, thr, sh);
-    if (at < 0) {
+    const int cross = block_cross(mass, inc, thr, sh);
+    if (cross < 0) {
       if (threadIdx.x == 0) sh.token = vocab - 1;
-    } else if ((int)threadIdx.x == at) {
+      __syncthreads();
+      return true;
+    }
+    if ((int)threadIdx.x == cross) sh.cap = inc - mass;
+    __syncthreads();
+    const double base = sh.cap;
+    const int end = min(vocab, ((cross >> 6) + 1) * per), run = (per + NT - 1) / NT;
+    const int lo = (cross >> 6) * per + (int)threadIdx.x * run, hi = min(end, lo + run);
+    double ts = 0.0;
+    for (int v0 = lo; v0 < hi; v0 += kBatch) {
+      double x[kBatch];
+      load_run(v0, hi, x);
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) ts += x[b];
+    }
+    const double tinc = base + block_scan(ts, sh);
+    const int at = block_cross(ts, tinc, thr, sh);
+    if ((int)threadIdx.x == (at < 0 ? 0 : at)) {
       int found = -1, last = lo;
-      double c = inc - ts;
-      for (int v = lo; v < hi; ++v) {
-        const double p = cur(v);
-        c += p;
-        if (p > 0.0) {
-          last = v;
-          if (found < 0 && c > thr) found = v;
+      double c = tinc - ts;
+      for (int v0 = lo; v0 < hi; v0 += kBatch) {
+        double x[kBatch];
+        load_run(v0, hi, x);
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+          c += x[b];
+          if (x[b] > 0.0) {
+            last = v0 + b;
+            if (found < 0 && c > thr) found = v0 + b;
+          }
         }
       }
       sh.token = found >= 0 ? found : last;
     }
+    __syncthreads();
     return true;
   }
 };
@@ -428,7 +516,7 @@ struct WalkRows {
   float u[kRows], qx[kRows];         // qx: q of the row at its token
   double px[kRows];                  // p of the row's parent at the row's token
   sb_row_stats st[kRows];
-  unsigned long long kmask[kNW];
+  unsigned long long kmask[kMemT / 64];
   int node, plen, nk, decision, flags;
 };
 static_assert(SB_MAX_ROWS <= kT, "a walk's rows have a thread each");
@@ -470,6 +558,7 @@ __device__ __forceinline__ bool accept(const WalkIn &a, const WalkRows &R, int c
 template <class D>
 __device__ bool walk_run(D &d, const WalkIn &a, WalkRows &R, WalkShared &sh, bool select, int *nrej,
                          int *bonus) {
+  constexpr int NT = D::kThreads;
   for (;;) {
     // While a node's first candidate is accepted against the node's own row,
     // the tests read LDS only, and one thread walks them.  The failing one is
@@ -487,7 +576,7 @@ __device__ bool walk_run(D &d, const WalkIn &a, WalkRows &R, WalkShared &sh, boo
     // the children of `node` in index order, one thread per row (a selection's
     // are all the other rows)
     if (select) {
-      for (int j = threadIdx.x + 1; j < a.n; j += kT) R.kids[j - 1] = (int16_t)j;
+      for (int j = threadIdx.x + 1; j < a.n; j += NT) R.kids[j - 1] = (int16_t)j;
       if (threadIdx.x == 0) R.nk = a.n - 1;
     } else {
       const int j = threadIdx.x, w = j >> 6;
@@ -497,15 +586,12 @@ __device__ bool walk_run(D &d, const WalkIn &a, WalkRows &R, WalkShared &sh, boo
       int before = __popcll(m & ((1ull << (j & 63)) - 1));
       for (int v = 0; v < w; ++v) before += __popcll(R.kmask[v]);
       if ((m >> (j & 63)) & 1) R.kids[before] = (int16_t)j;
-      if (j == kT - 1) R.nk = before + (int)((m >> 63) & 1);
+      if (j == NT - 1) R.nk = before + (int)((m >> 63) & 1);
     }
     __syncthreads();
     const int nk = R.nk;
     d.set_row(row_of(a, R.st[node]), a.logits + (size_t)node * a.vocab);
-    if (nk == 0) {
-      *bonus = 1;
-      return d.draw(a.u[a.u_draw], sh);
-    }
+    *bonus = nk == 0;
     int acc = -1;
     bool resid = false;  // p~ is a residual
     double px_at = 0.0;  // p~ at the next candidate's token, once it is
@@ -548,9 +634,10 @@ __device__ bool walk_run(D &d, const WalkIn &a, WalkRows &R, WalkShared &sh, boo
 }
 
 // The rows' values, before the first test.
+template <int NT>
 __device__ void walk_rows(const WalkIn &a, const TreeArg *tree, WalkRows &R) {
   const int n = a.n;
-  for (int i = threadIdx.x; i < n; i += kT) {
+  for (int i = threadIdx.x; i < n; i += NT) {
     R.par[i] = tree ? tree->parent[i] : (int16_t)(i == 0 ? -1 : 0);
     if (tree || i == 0) R.st[i] = a.stats[i];
     R.tok[i] = i >= a.off ? a.tokens[i - a.off] : -1;
@@ -559,7 +646,7 @@ __device__ void walk_rows(const WalkIn &a, const TreeArg *tree, WalkRows &R) {
   }
   if (threadIdx.x == 0) R.flags = 0;
   __syncthreads();
-  for (int i = threadIdx.x; i < n; i += kT) {
+  for (int i = threadIdx.x; i < n; i += NT) {
     if ((tree || i == 0) && isnan(R.st[i].total)) atomicOr(&R.flags, SB_FLAG_NONFINITE);
     if (i == 0) continue;
     const int par = R.par[i], x = R.tok[i];
@@ -584,13 +671,14 @@ __device__ void walk_rows(const WalkIn &a, const TreeArg *tree, WalkRows &R) {
 
 // EPT tokens per thread (0: one workgroup, p~ in memory).
 template <int EPT, bool SELECT>
-__global__ __launch_bounds__(kT) void k_walk(WalkIn a, TreeArg tree, int vec4, WalkWait wait,
+__global__ __launch_bounds__(EPT ? kT : kMemT) void k_walk(WalkIn a, TreeArg tree, int vec4, WalkWait wait,
                                              sb_step_result *__restrict__ result,
                                              int32_t *__restrict__ out,
                                              unsigned long long *msg, double *arr) {
+  constexpr int NT = EPT ? kT : kMemT;
   __shared__ WalkRows R;
   __shared__ WalkShared sh;
-  walk_rows(a, SELECT ? nullptr : &tree, R);
+  walk_rows<NT>(a, SELECT ? nullptr : &tree, R);
   int nrej = 0, bonus = 0;
   bool done = false;
   if constexpr (EPT > 0) {
@@ -600,9 +688,9 @@ __global__ __launch_bounds__(kT) void k_walk(WalkIn a, TreeArg tree, int vec4, W
   }
   if (blockIdx.x != 0) return;  // the result is workgroup 0's alone
   if (!done) {
-    if (EPT > 0) walk_rows(a, SELECT ? nullptr : &tree, R);
+    if (EPT > 0) walk_rows<NT>(a, SELECT ? nullptr : &tree, R);
     nrej = bonus = 0;
-    InMemory d;
+    InMemory<NT> d;
     d.vocab = a.vocab;
     d.arr = arr;
     walk_run(d, a, R, sh, SELECT, &nrej, &bonus);
@@ -632,7 +720,7 @@ __global__ __launch_bounds__(kT) void k_walk(WalkIn a, TreeArg tree, int vec4, W
       result->bonus = bonus;
       result->reserved = 0;
     }
-    for (int j = threadIdx.x; j < SB_MAX_ROWS; j += kT)
+    for (int j = threadIdx.x; j < SB_MAX_ROWS; j += NT)
       result->path[j] = j < R.plen ? (int32_t)R.path[j] : -1;
   }
 }
@@ -646,14 +734,14 @@ __global__ __launch_bounds__(kT) void k_walk_clear(unsigned long long *p, int n)
 template <bool SELECT>
 hipError_t launch(const WalkIn &a, const TreeArg &tree, sb_step_result *result, int32_t *out,
                   void *ws, hipStream_t s, const WalkWait &wait) {
-  double *arr = (double *)ws;  // 2 vocab float64: the residual, then the messages
+  double *arr = (double *)ws;  // 2 vocab float64: p~ in memory, then the messages
   unsigned long long *msg = (unsigned long long *)(arr + a.vocab);
   const int vec4 = (a.vocab & 3) == 0;
   int ept = 4;
   while (ept < 32 && (a.vocab + kT * ept - 1) / (kT * ept) > 64) ept *= 2;
   const int G = (a.vocab - 1) / (kT * ept) + 1;
   if (G > kMaxG) {
-    hipLaunchKernelGGL((k_walk<0, SELECT>), dim3(1), dim3(kT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
+    hipLaunchKernelGGL((k_walk<0, SELECT>), dim3(1), dim3(kMemT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
     return hipGetLastError();
   }
   if (G > 1) {

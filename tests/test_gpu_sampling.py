@@ -376,6 +376,83 @@ def test_walk_nonfinite_row(api, vocab, bad, T):
             assert (got["n_rejected"], bool(got["bonus"])) == (ref.n_rejected, ref.bonus)
 
 
+def _four_rejected(vocab, seed):
+    """As _all_rejected with four candidates, the second one's row twice the
+    distribution it is tested against, which leaves a residual without mass;
+    the third one's ratio is 0.8."""
+    lg, p, q, toks, u = _all_rejected(vocab, 4, 1.0, seed)
+    pt = sampling.branch_select(p, toks[:1], q[:1], u[:1]).p_tilde
+    q[1] = (2.0 * pt).astype(np.float32)
+    toks[1] = toks[2] = np.argmax(pt[:-1])
+    q[2, toks[2]] = pt[toks[2]] / 0.8
+    return lg, p, q, toks, u
+
+
+@pytest.mark.parametrize("vocab", [1000, 1025, 65536, 65537, 131073, 262145, 2097152, 2097153])
+@pytest.mark.parametrize("alone", [False, True])
+def test_select_draws(api, vocab, alone):
+    """Draws after four rejections, the second of them without mass, that cross
+    in the first, a middle and the last slice of the vocabulary (one token
+    where the vocabulary is one past whole slices): by each slice width, by
+    workgroup 0 alone after it gave up, and past the slices' reach."""
+    lg, p, q, toks, u = _four_rejected(vocab, 900 + vocab)
+    sel = sampling.branch_select(p, toks, q, u)
+    assert sel.accepted is None and sel.flags == sampling.FLAG_ZERO_RESIDUAL
+    st = api.new_stats(1)
+    dl, dt, dq = dev(lg), dev(toks), dev(q)
+    api.sb_softmax_stats(dl[None], 1.0, st)
+    ws = torch.empty(api.sb_sample_workspace_bytes(vocab), dtype=torch.uint8, device="cuda")
+    f = api.lib.sb_internal_select_branch
+    f.restype = C.c_int32
+    f.argtypes = api.lib.sb_select_branch.argtypes + [C.c_uint64] + [C.c_int32] * 3
+    per = _slice_tokens(vocab)
+    last = (vocab - 1) // per
+
+    def select(*uniforms):
+        out = torch.full((3,), -7, dtype=torch.int32, device="cuda")
+        du = dev(np.asarray(uniforms, np.float32))
+        assert f(vocab, dl.data_ptr(), st.data_ptr(), 1.0, 4, dt.data_ptr(), dq.data_ptr(), du.data_ptr(), out.data_ptr(),
+                 ws.data_ptr(), ws.numel(), api._stream(), 100000, 0, int(alone), 0) == 0
+        return out.cpu().tolist()
+
+    # the test after the rejection without mass reads p~ as it was before it
+    say(f"select draws vocab={vocab} third candidate alone={alone}")
+    assert select(0.9, 0.9, 0.7, 0.9, 0.5) == [2, toks[2], sampling.FLAG_ZERO_RESIDUAL]
+    for g in sorted({0, last // 2, last}):
+        uf = _uniform_into(sel.p_tilde, g * per, min(vocab, (g + 1) * per))
+        tr = []
+        sampling.branch_select(p, toks, q, u, trace=tr)
+        want = sampling.draw(sel.p_tilde, float(uf), tr, 4)
+        assert want // per == g
+        assert decision_margin(tr, np.append(u, uf)) > TIE
+        say(f"select draws vocab={vocab} slice {g} of {last + 1} alone={alone}")
+        assert select(*u, uf) == [-1, want, sampling.FLAG_ZERO_RESIDUAL]
+
+
+def test_select_past_the_slices_time(api):
+    """One workgroup does a vocabulary past the slices' reach; reading along it,
+    three rejections and a draw over 2.1 million tokens take 2 ms (24 ms when a
+    thread summed a stretch of its own)."""
+    vocab = 2100001
+    lg, p, q, toks, u = _all_rejected(vocab, 3, 1.0, 5)
+    st = api.new_stats(1)
+    dl, dt, dq, du = dev(lg), dev(toks), dev(q), dev(np.append(u, np.float32(0.5)).astype(np.float32))
+    api.sb_softmax_stats(dl[None], 1.0, st)
+    ws = torch.empty(api.sb_sample_workspace_bytes(vocab), dtype=torch.uint8, device="cuda")
+    out = torch.zeros(3, dtype=torch.int32, device="cuda")
+    best = 1e9
+    for _ in range(4):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        api.sb_select_branch(dl, st, 1.0, dt, dq, du, out, ws)
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    print(f"select at {vocab} tokens: {best:.2f} ms", flush=True)
+    assert out[0].item() == -1
+    assert best < 8.0
+
+
 def test_walk_flags(api):
     vocab = 64
     parents = synth.branch_parents(2, 2)

@@ -240,7 +240,15 @@ sb_status sb_verify_forward_noalloc(sb_model *m, const sb_kv_cache *kv, int32_t 
 sb_status sb_softmax_stats(int32_t vocab, int32_t n_rows, const float *d_logits,
                            float temperature, sb_row_stats *d_stats, hipStream_t stream);
 
-/* Workspace bytes of sb_select_branch / sb_accept_resample for a vocab. */
+/* Workspace bytes of sb_select_branch / sb_accept_resample for a vocab.
+ *
+ * Both run on up to 256 workgroups that wait for each other's sums, in an
+ * ordinary launch.  Where other work (a forward on another stream, another
+ * process) keeps some of them off the device for 0.2 ms, the others give up and
+ * one workgroup finishes alone, with p~ in the workspace: the same decisions
+ * to the rounding of the float64 sums, later by 0.1 ms at 32000 tokens and 0.3 at
+ * 128256.  An SB_FWD_PERSISTENT forward beside them, which needs every compute
+ * unit at once, can be held up for these times. */
 size_t sb_sample_workspace_bytes(int32_t vocab);
 
 /* Algorithm 1 (Branch Speculative Sampling) at one node.

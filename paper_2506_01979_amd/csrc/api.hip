@@ -817,7 +817,8 @@ size_t sb_sample_workspace_bytes(int32_t vocab) {
 }
 
 // sb_select_branch and sb_accept_resample with the walk's waits as arguments
-// (WalkWait), for the tests of what a workgroup that gives up leaves behind.
+// (WalkWait; ticks 0: theirs), for the tests of what a workgroup that gives up
+// leaves behind.
 sb_status sb_internal_select_branch(int32_t vocab, const float *d_logits_row,
                                     const sb_row_stats *d_stats_row, float temperature,
                                     int32_t n_cand, const int32_t *d_cand_tokens, const float *d_q,
@@ -831,7 +832,7 @@ sb_status sb_internal_select_branch(int32_t vocab, const float *d_logits_row,
   if (ws_bytes < sample_ws_bytes(vocab)) return SB_ERR_CAPACITY;
   return hip_status(launch_select(vocab, d_logits_row, d_stats_row, temperature, n_cand,
                                   d_cand_tokens, d_q, d_u, d_out, d_ws, stream,
-                                  WalkWait{ticks, lo, hi, at}));
+                                  WalkWait{ticks ? ticks : kWalkWait.ticks, lo, hi, at}));
 }
 
 sb_status sb_internal_accept_resample(int32_t vocab, int32_t n_rows, const int32_t *d_tokens,
@@ -848,7 +849,7 @@ sb_status sb_internal_accept_resample(int32_t vocab, int32_t n_rows, const int32
   if (st != SB_OK) return st;
   if (ws_bytes < sample_ws_bytes(vocab)) return SB_ERR_CAPACITY;
   return hip_status(launch_walk(vocab, tree, d_tokens, d_logits, d_stats, temperature, d_q, d_u,
-                                d_result, d_ws, stream, WalkWait{ticks, lo, hi, at}));
+                                d_result, d_ws, stream, WalkWait{ticks ? ticks : kWalkWait.ticks, lo, hi, at}));
 }
 
 sb_status sb_select_branch(int32_t vocab, const float *d_logits_row,

@@ -35,14 +35,17 @@ struct LmPart {
 hipError_t launch_stats_finish(const LmPart *part, int groups, int n_rows, float temperature,
                                sb_row_stats *stats, hipStream_t s);
 // How long a workgroup of the walk waits for the others' messages: ticks of the
-// 100 MHz s_memrealtime counter (50 ms; they arrive within microseconds unless
-// the chip cannot hold them all).  Workgroups lo .. hi - 1 do not wait at all
-// from exchange `at` on (for tests; none otherwise).
+// 100 MHz s_memrealtime counter.  They arrive within microseconds unless other
+// work keeps some workgroups off the chip; that work may itself wait for the
+// compute units the walk holds (a persistent forward on another stream), so the
+// limit is about what the walk takes one workgroup alone: 0.2 ms (79 us at 32000
+// tokens, 257 at 128256).  Workgroups lo .. hi - 1 do not wait at all from
+// exchange `at` on (for tests; none otherwise).
 struct WalkWait {
   unsigned long long ticks;
   int lo, hi, at;
 };
-constexpr WalkWait kWalkWait{5000000ull, 0, 0, 0};
+constexpr WalkWait kWalkWait{20000ull, 0, 0, 0};
 hipError_t launch_walk(int vocab, const TreeArg &tree, const int32_t *tokens, const float *logits,
                        const sb_row_stats *stats, float temperature, const float *q,
                        const float *u, sb_step_result *result, void *ws, hipStream_t s,

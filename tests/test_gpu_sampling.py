@@ -453,6 +453,37 @@ def test_select_past_the_slices_time(api):
     assert best < 8.0
 
 
+def test_walk_wait_is_short(api):
+    """Where one workgroup's messages never come, the others stop waiting after
+    0.2 ms each (at most once per workgroup: who gives up leaves), and workgroup
+    0 alone ends the walk: a call delayed by other work on the chip is late by
+    well under a millisecond, not by the tens it would be worth waiting."""
+    vocab = 32000
+    lg, p, q, toks, u = _all_rejected(vocab, 3, 1.0, 6)
+    sel = sampling.branch_select(p, toks, q, u)
+    uf = _uniform_into(sel.p_tilde, 0, vocab)
+    st = api.new_stats(1)
+    dl, dt, dq, du = dev(lg), dev(toks), dev(q), dev(np.append(u, uf).astype(np.float32))
+    api.sb_softmax_stats(dl[None], 1.0, st)
+    ws = torch.empty(api.sb_sample_workspace_bytes(vocab), dtype=torch.uint8, device="cuda")
+    out = torch.zeros(3, dtype=torch.int32, device="cuda")
+    f = api.lib.sb_internal_select_branch
+    f.restype = C.c_int32
+    f.argtypes = api.lib.sb_select_branch.argtypes + [C.c_uint64] + [C.c_int32] * 3
+    best = 1e9
+    for _ in range(4):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        assert f(vocab, dl.data_ptr(), st.data_ptr(), 1.0, 3, dt.data_ptr(), dq.data_ptr(), du.data_ptr(), out.data_ptr(),
+                 ws.data_ptr(), ws.numel(), api._stream(), 0, 1, 2, 0) == 0
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+        assert out.cpu().tolist() == [-1, sampling.draw(sel.p_tilde, float(uf)), 0]
+    print(f"selection with one workgroup gone: {best:.2f} ms", flush=True)
+    assert best < 2.0
+
+
 def test_walk_flags(api):
     vocab = 64
     parents = synth.branch_parents(2, 2)

@@ -193,8 +193,8 @@ struct BranchArgs {
   double *znorm;   // [SB_BRANCH_MAX_K] workspace: the mass before each draw
 };
 hipError_t launch_branch(const BranchArgs &a, hipStream_t s);
-// Launch geometry of a GEMM: token tiles (rounded up to a kernel's), tiles per
-// pass, K split, tile groups and grid.
+// Launch geometry of a GEMM: token tiles (of a token block), tiles per pass, K
+// split, tile groups and grid.
 // Largest tiles per pass of k_gemm (its register budget), and the (tile,
 // token tile) accumulator pairs it reduces per LDS round.
 constexpr int kGemmNtCap = 8;

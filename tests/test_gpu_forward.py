@@ -7,7 +7,7 @@ rows must match to the same bound.  Shapes span several GEMM tiles, ragged K
 (ffn 688, 600), ragged vocabularies (1000, 1001), a hidden width that is not
 a multiple of 16 (328), ragged attention chunks, GQA, both head widths and
 5..137-row trees (the O projection applies the post-attention RMSNorm up to
-128 rows and hands it to a separate kernel above), the paper's
+64 rows and hands it to a separate kernel above), the paper's
 chain-plus-fork verification shape (a chain of drafts, then B candidates
 with or without continuations), and 32 KV heads on a narrow model (few key
 ranges per head).  Invariant (a) -- branch-masked rows equal
@@ -56,10 +56,13 @@ def mode(shape):
 
 def gpu_forward(api, m, Kp, Vp, kv_len, tokens, parents, T=1.0, cap=None, stats_out=None):
     """Logits and cache of one sb_verify_forward call; the row statistics
-    are appended to stats_out when given."""
+    are appended to stats_out when given.  Cache slots past the prefix hold
+    NaN: a forward reads none that it has not written."""
     n = len(parents)
     cap = cap or kv_len + n + 8
     k, v = m.new_kv(cap)
+    k.fill_(float("nan"))
+    v.fill_(float("nan"))
     if kv_len:
         m.load_kv(k, v, Kp, Vp, kv_len)
     logits = torch.empty((n, m.shape.vocab), dtype=torch.float32, device="cuda")
@@ -115,15 +118,16 @@ CASES = [
     # trees of 65 .. 80 rows (5 token tiles)
     ("small_gqa_bf16", 300, ("branch", 8, 8)),
     ("small_h128_bf16", 100, ("branch", 5, 15)),
-    # more than 16 rounds of (KV head, key range, row block) units: each
-    # workgroup walks the three row blocks of its key range
+    # a long prefix read by 9 row tiles of every KV head (k_attn_rows: 8 ranges
+    # of 43 or 44 steps)
     ("heads32_bf16", 11000, ("branch", 8, 16)),
-    # long prefixes over many one-step workgroups (head_dim 64 and 128, one
-    # and three row blocks, grouped queries, up to 95 key ranges)
+    # long prefixes: few long ranges (k_attn_rows, one and more row blocks,
+    # grouped queries) and many one-step workgroups (k_attn, 33 rows), head_dim
+    # 64 and 128
     ("heads32_bf16", 3000, ("branch", 8, 16)),
     ("heads32_bf16", 5000, ("branch", 4, 8)),
     ("gqa128_bf16", 24000, ("branch", 8, 16)),
-    # trees of 145 .. 192 rows (12 token tiles in the wide GEMMs)
+    # trees of 145 .. 192 rows (two token blocks in the wide GEMMs)
     ("ragged_bf16", 90, ("branch", 10, 17)),
     ("small_h128_bf16", 500, ("branch", 12, 13)),
     # the largest trees (SB_MAX_ROWS = 256 rows): 15 x 17 branches, a
@@ -284,14 +288,15 @@ def test_attention_row_tiles(api, heads, kv, d, P, n):
     assert row_relerr(vg.reshape(-1, d), vt.reshape(-1, d)) < tol(shape) * 5
 
 
+@pytest.mark.parametrize("branches,depth", [(3, 4), (6, 14)])  # 13 rows: with the LM head; 85: a pass of its own
 @pytest.mark.parametrize("sname,kind,T", [
     ("small_bf16", "ties", 1.0), ("small_bf16", "ties", 0.0), ("ragged_bf16", "ties", 0.7),
     ("small_bf16", "nonfinite", 1.0), ("small_bf16", "nonfinite", 0.0),
     ("ragged_bf16", "nonfinite", 1.3),
 ])
-def test_forward_statistics_special_rows(api, sname, kind, T):
-    """The statistics computed with the LM head on logits with ties and
-    non-finite values.  ties: every LM-head row zero except rows 100 .. 199,
+def test_forward_statistics_special_rows(api, sname, kind, T, branches, depth):
+    """The statistics of a forward (up to 64 rows computed with the LM head, above
+    by a pass of their own) on logits with ties and non-finite values.  ties: every LM-head row zero except rows 100 .. 199,
     which share one vector, so each row of logits is 0 except one value
     repeated 100 times (the largest is tied, its lowest index wins, and the
     1000-odd equal zeros enter the total).  nonfinite: row 7 of the LM head
@@ -307,9 +312,9 @@ def test_forward_statistics_special_rows(api, sname, kind, T):
     else:
         lm[7] = np.inf
     W["lm_head"] = lm
-    say(f"forward statistics {sname} {kind} T={T}")
+    say(f"forward statistics {sname} {kind} T={T} rows={1 + branches * depth}")
     m = api.Model(shape, api.dict_tensors(W))
-    P, parents = 60, synth.branch_parents(3, 4)
+    P, parents = 60, synth.branch_parents(branches, depth)
     ptoks = synth.prefix_tokens(shape.vocab, P)
     _, Kp, Vp = decoder.prefill(shape, weights(shape), ptoks[:-1], "bf16")
     toks = np.random.default_rng(5).integers(0, shape.vocab, len(parents)).astype(np.int32)

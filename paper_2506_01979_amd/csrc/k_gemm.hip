@@ -27,10 +27,6 @@ constexpr int kNTs[] = {1, 2, 3, 4, 6, 8};
 
 }  // namespace
 
-// Token tiles past which every projection takes k_gemm_wide (its comment has
-// both sides measured: at 5 tiles it is ahead on all of them, at 3 behind).
-constexpr int kWideFrom = 4;
-
 // Wide plan: the fewest token blocks of at most kWideTtCap tiles; the tile
 // groups fill the compute units; a group's tiles go in as few passes over K
 // as the accumulators allow.  The residual projections also split K over the
@@ -94,8 +90,7 @@ GemmPlan plan_gemm(int epi, int tiles, int ks, int n_tok) {
   int groups = cus / S;
   if (groups > tiles) groups = tiles;
   const int per_wg = (tiles + groups - 1) / groups;
-  const int cap = kGemmNtCap;
-  const int passes = (per_wg + cap - 1) / cap;
+  const int passes = (per_wg + kGemmNtCap - 1) / kGemmNtCap;
   const int need = (per_wg + passes - 1) / passes;
   for (int v : kNTs)
     if (v >= need) {

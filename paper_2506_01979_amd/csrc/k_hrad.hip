@@ -31,7 +31,11 @@ __device__ __forceinline__ bool hrad_source(const HradArgs &a, int *row, int *to
 // consecutive inputs per step (hidden is a multiple of 8, so 4 never straddle
 // two parts of z).  Bound by W1 from memory (21 MB at hidden 4096 and 4 taps):
 // the weights of kL1Batch steps go out before the row and the token, a chain
-// of three dependent reads, are looked up.
+// of three dependent reads, are looked up.  A batch is 20480 inputs; wider
+// features take the rest after it, narrower ones read past the row's end (zero,
+// no traffic).  Both launches, host to host, against loads as they are needed:
+// 4 taps at hidden 512 to 4096 14.5 -> 12 us, at 5120 (25 steps) 18 -> 12, at
+// 8192 (40) 27 -> 17.
 __global__ __launch_bounds__(kL1Threads) void k_hrad_l1(HradArgs a) {
   __shared__ float red[kL1Threads / 64];
   const int j = blockIdx.x;

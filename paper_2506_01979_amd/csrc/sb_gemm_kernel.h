@@ -142,6 +142,7 @@ struct Ring {
 // tokens (the consumer of a RESID_NORM launch).
 constexpr int kStageBytes = 32768;
 constexpr int kRopeLds = kStageBytes / 8;  // float2 entries
+static_assert(16 * kWideFrom * 128 / 2 <= kRopeLds, "k_gemm's rows at head_dim 128");
 constexpr int kStageGain = 16384;          // RESID_NORM: gains (1 KB)
 constexpr int kStageSq = 17408;            // RESID_NORM: per-(tile, token) sums of squares
 constexpr int kStageLmSlot = 0;            // LOGITS: statistics per (part, token), 8 KB
@@ -294,8 +295,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void k_gemm(GemmArgs a) {
   // epilogue needs them.
   // QKV: the step's RoPE table (its buffer holds whole 1 KB blocks: rows
   // padded to 16).
-  const bool rope_lds = EPI == EPI_QKV && a.n_tok * (a.head_dim / 2) <= kRopeLds;
-  if (rope_lds) {
+  if constexpr (EPI == EPI_QKV) {
     const int nblk = (a.n_tok * (a.head_dim / 2) * 8 + 1023) >> 10;
     for (int b = w; b < nblk; b += kGemmWaves)
       __builtin_amdgcn_global_load_lds((const void *)((const char *)a.rope + b * 1024 + lane * 16),
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void k_gemm(GemmArgs a) {
       if (t < a.n_tok && qtr == 0) sinv[t] = 1.0f / sqrtf(sum / (float)a.norm_dim + a.eps);
       lds_barrier();  // the scales are visible, the reduction buffer is free
     }
-    const float2 *rope = rope_lds ? (const float2 *)stage : a.rope;
+    const float2 *rope = (const float2 *)stage;
     const float *sh = (const float *)stage;                  // RESID_NORM residual blocks
     const float *sg = (const float *)(stage + kStageGain);   // RESID_NORM gains
     float *ssq = (float *)(stage + kStageSq);                // RESID_NORM [tile][token]
@@ -791,19 +791,15 @@ hipError_t launch_wide(const GemmArgs &a, const GemmPlan &p, hipStream_t s) {
 
 template <int EPI, int TT, int NT>
 hipError_t launch_tt_nt(const GemmArgs &a, int grid, hipStream_t s) {
-  if constexpr (NT > kGemmNtCap) {
-    return hipErrorInvalidValue;
+  LaunchEvents &ev = g_launch_events;
+  if (!ev.taken) {
+    ev.taken = true;
+    hipExtLaunchKernelGGL((k_gemm<EPI, TT, NT>), dim3(grid), dim3(kGemmThreads), 0, s, ev.start,
+                          ev.stop, 0, a);
   } else {
-    LaunchEvents &ev = g_launch_events;
-    if (!ev.taken) {
-      ev.taken = true;
-      hipExtLaunchKernelGGL((k_gemm<EPI, TT, NT>), dim3(grid), dim3(kGemmThreads), 0, s, ev.start,
-                            ev.stop, 0, a);
-    } else {
-      hipLaunchKernelGGL((k_gemm<EPI, TT, NT>), dim3(grid), dim3(kGemmThreads), 0, s, a);
-    }
-    return hipGetLastError();
+    hipLaunchKernelGGL((k_gemm<EPI, TT, NT>), dim3(grid), dim3(kGemmThreads), 0, s, a);
   }
+  return hipGetLastError();
 }
 
 template <int EPI, int TT>

@@ -198,6 +198,9 @@ hipError_t launch_branch(const BranchArgs &a, hipStream_t s);
 // Largest tiles per pass of k_gemm (its register budget), and the (tile,
 // token tile) accumulator pairs it reduces per LDS round.
 constexpr int kGemmNtCap = 8;
+// Token tiles past which every projection takes k_gemm_wide (its comment has
+// both sides measured: at 5 tiles it is ahead on all of them, at 3 behind).
+constexpr int kWideFrom = 4;
 constexpr int kRedPairs = 16;
 // k_gemm_wide: most (tile, token tile) accumulator pairs and tiles of a pass,
 // most token tiles of a workgroup.

@@ -729,40 +729,40 @@ __global__ __launch_bounds__(kT) void k_walk_clear(unsigned long long *p, int n)
   for (int i = threadIdx.x; i < n; i += kT) p[i] = 0;
 }
 
-// 1024 tokens a workgroup while 64 of them reach, then twice as many; past
-// 256 workgroups of 8192 one workgroup with p~ in memory.
+// One workgroup up to 2048 tokens, and up to 4096 in 16-byte loads: no messages,
+// and not the launch that clears them, which small vocabularies do not earn
+// back.  Several workgroups -> one, us: every draft accepted, 1500 tokens 11.2 ->
+// 8.8, 4000 11.1 -> 9.9; three rejections 16.0 -> 11.7, 15.1 -> 14.1; with rows of
+// 4001 11.1 -> 11.4 and 17.3 -> 18.4, with 32 tokens a thread (8000) 11.4 -> 12.0
+// and 16.7 -> 19.1, with 1024 threads instead slower still.  Above, 1024 tokens a
+// workgroup while 64 of them reach, then twice as many; past 256 workgroups of
+// 8192 one workgroup with p~ in memory.
 template <bool SELECT>
 hipError_t launch(const WalkIn &a, const TreeArg &tree, sb_step_result *result, int32_t *out,
                   void *ws, hipStream_t s, const WalkWait &wait) {
   double *arr = (double *)ws;  // 2 vocab float64: p~ in memory, then the messages
   unsigned long long *msg = (unsigned long long *)(arr + a.vocab);
   const int vec4 = (a.vocab & 3) == 0;
+  auto go = [&](auto kernel, int grid, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, a, tree, vec4, wait, result, out, msg, arr);
+    return hipGetLastError();
+  };
+  if (a.vocab <= 4 * kT) return go(k_walk<4, SELECT>, 1, kT);
+  if (a.vocab <= 8 * kT) return go(k_walk<8, SELECT>, 1, kT);
+  if (a.vocab <= 16 * kT && vec4) return go(k_walk<16, SELECT>, 1, kT);
   int ept = 4;
   while (ept < 32 && (a.vocab + kT * ept - 1) / (kT * ept) > 64) ept *= 2;
   const int G = (a.vocab - 1) / (kT * ept) + 1;
-  if (G > kMaxG) {
-    hipLaunchKernelGGL((k_walk<0, SELECT>), dim3(1), dim3(kMemT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
-    return hipGetLastError();
-  }
-  if (G > 1) {
-    hipLaunchKernelGGL(k_walk_clear, dim3(1), dim3(kT), 0, s, msg, 1 + 2 * G);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  if (G > kMaxG) return go(k_walk<0, SELECT>, 1, kMemT);
+  hipLaunchKernelGGL(k_walk_clear, dim3(1), dim3(kT), 0, s, msg, 1 + 2 * G);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   switch (ept) {
-    case 4:
-      hipLaunchKernelGGL((k_walk<4, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
-      break;
-    case 8:
-      hipLaunchKernelGGL((k_walk<8, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
-      break;
-    case 16:
-      hipLaunchKernelGGL((k_walk<16, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
-      break;
-    default:
-      hipLaunchKernelGGL((k_walk<32, SELECT>), dim3(G), dim3(kT), 0, s, a, tree, vec4, wait, result, out, msg, arr);
+    case 4: return go(k_walk<4, SELECT>, G, kT);
+    case 8: return go(k_walk<8, SELECT>, G, kT);
+    case 16: return go(k_walk<16, SELECT>, G, kT);
+    default: return go(k_walk<32, SELECT>, G, kT);
   }
-  return hipGetLastError();
 }
 
 WalkIn walk_in(int vocab, int n, float temperature, const int32_t *tokens, const float *logits,

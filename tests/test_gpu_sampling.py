@@ -382,7 +382,7 @@ def _four_rejected(vocab, seed):
     return lg, p, q, toks, u
 
 
-@pytest.mark.parametrize("vocab", [1000, 1025, 65536, 65537, 131073, 262145, 2097152, 2097153])
+@pytest.mark.parametrize("vocab", [1000, 1025, 2048, 2049, 4096, 4097, 65536, 65537, 131073, 262145, 2097152, 2097153])
 @pytest.mark.parametrize("alone", [False, True])
 def test_select_draws(api, vocab, alone):
     """Draws after four rejections, the second of them without mass, that cross

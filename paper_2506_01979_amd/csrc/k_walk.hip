@@ -25,9 +25,12 @@
 // finds to workgroup 0, which alone writes the result: when any message it
 // needs stays out (a workgroup that gave up, or that the chip has no room for)
 // it does the walk again by itself with p~ in memory.  Measured (the walk
-// with a rejection or two, one workgroup of 1024 threads -> these): 37 rows at
-// 128256 tokens 61 -> 11 us, 33 rows at 32000 tokens 23 -> 12 us, and 1.4 us
-// for the launch that clears the messages.
+// and the launch that clears the messages, in turn on an idle device; one
+// workgroup of 1024 threads -> these): a chain rejected at its first draft, 32000
+// tokens 20 -> 13 us, 128256 tokens 54 -> 14; a chain accepted whole 14 -> 12 and
+// 29 -> 13; a selection with three rejections 45 -> 19 and 156 -> 21, one accepted
+// at once 8 -> 10 to 12 (the clearing launch: 4.6 us in a kernel trace, of which
+// 2 to 3 show).  The token's way to workgroup 0 is about 1 us of these.
 #pragma clang fp contract(off)
 
 #include <limits.h>

@@ -578,12 +578,13 @@ __global__ __launch_bounds__(kGemmThreads, 1) void k_gemm(GemmArgs a) {
 // with no LDS and no barrier in the main loop.  More than 9 token tiles are
 // cut into two token blocks, in workgroups next to each other on one XCD
 // (they share the weights through its L2).  Measured against the form that
-// staged the activation through LDS for 8 waves (13B, 129 rows / 7B, 256
-// rows): QKV 63 -> 43 / 90 -> 38 us, gate/up 81 -> 68 / 91 -> 70, down 49 ->
-// 35 / 57 -> 36, O 25 -> 18 / 30 -> 19; at 65 rows against k_gemm: gate/up 62 -> 48, down 39 ->
-// 27, QKV 36 -> 32, LM head 79 -> 56.  At 33 rows k_gemm's deeper ring and 8
-// waves win (QKV 27 against 28, O 11 against 13), so this form starts at 5
-// token tiles.  The activation through a ring in LDS (direct-to-LDS loads,
+// staged the activation through LDS for 8 waves, 13B at 129 rows (kernel trace of
+// the step): QKV 62 -> 46 us, gate/up 77 -> 61, down 48 -> 37, O 25 -> 19; the LM
+// head, which needs two passes over the activation here, 78 -> 90.  7B at 256
+// rows (event-timed): QKV 90 -> 38, gate/up 91 -> 70, down 57 -> 36, O 30 -> 19; at
+// 65 rows against k_gemm: gate/up 62 -> 48, down 39 -> 27, QKV 36 -> 32, LM head
+// 79 -> 56.  At 33 rows k_gemm's deeper ring and 8 waves win (QKV 27 against 28,
+// O 11 against 13), so this form starts at 5 token tiles.  The activation through a ring in LDS (direct-to-LDS loads,
 // 1.5 to 2 times the bytes in flight) measured level with it.
 constexpr int kWideThreads = 256;
 constexpr int kWideWaves = kWideThreads / 64;
@@ -591,9 +592,9 @@ constexpr int kWideRedPairs = 40;  // accumulators per LDS reduction round (160 
 constexpr int kPastEnd = 0x40000000;  // a scalar offset past the end of any operand of a pass
 
 // Ring depth: as many steps as about 200 registers hold, at most 6; two for
-// the 9 x 7 form, which spills with three (13B gate/up at 129 rows: 58 us with
-// 2, 80 with 3; the 8 x 8 form does not: 7B LM head at 256 rows, 2 slots 118
-// us, 3 slots 94).
+// the 9 x 7 form, which spills with three (13B gate/up at 129 rows, both in one
+// run: 58 us with 2, 80 with 3; the 8 x 8 form does not: 7B LM head at 256 rows,
+// 2 slots 118 us, 3 slots 94).
 template <int TT, int NT>
 struct WideRing {
   static constexpr int r = 212 / (4 * (NT + TT));
